@@ -301,10 +301,13 @@ pa_status pa_stream_probe(const pa_dims* dims, const char* call, const void* x,
  * one hipBLASLt handle there (kept until the process ends); ws/ws_bytes is
  * hipBLASLt's workspace (may be 0).  pa_gemm itself never synchronises: a
  * problem (shape, dtypes, transposes, bias) that pa_gemm_prepare has not
- * tuned runs hipBLASLt's first heuristic candidate.  A long reduction into a small fp32 output (transA, K >= 2^17, D at most
- * 8 MB, beta = 0, no bias: the weight gradients) is split over K into up to
- * 64 partial products kept at the end of ws (at most half of it) and added
- * in order, deterministically.  A combination of dtypes hipBLASLt does
+ * tuned runs hipBLASLt's first heuristic candidate.   A long reduction into a small
+ * fp32 output (transA, beta = 0, no bias: the weight gradients) runs the
+ * library's own kernel (A and B of one type, m and n multiples of 64, D at
+ * most 8 MB; fp32 up to 2^17 points) or, from K = 2^17, hipBLASLt products
+ * split over K.  Both keep up to 256 partial products at the end of ws (at
+ * most half of it) and add them in order, deterministically; long
+ * reductions want a workspace (64 MB serves every such product).  A combination of dtypes hipBLASLt does
  * not serve returns PA_ERR_UNSUPPORTED. */
 pa_status pa_gemm(int transA, int transB, int64_t m, int64_t n, int64_t k, float alpha,
                   const void* A, pa_dtype a_dtype, const void* B, pa_dtype b_dtype,

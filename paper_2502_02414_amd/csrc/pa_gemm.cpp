@@ -176,14 +176,38 @@ static int gemm_once(const Gemm& g, int batch, int64_t sa, int64_t sb, int64_t s
 }
 
 int gemm(const Gemm& g, hipStream_t st, bool tune) {
-  // A long reduction into a small fp32 output -- the weight gradients, op(A)
-  // = X^T with K the points -- is split over K: S strided-batched products
-  // of kc rows each (plus one for the rest) write S fp32 partials at the end
-  // of the workspace, added in order into D by the ordered reduction
-  // (deterministic; the whole GPU works on S times as many output tiles).
+  // Weight gradients: the library's own kernel, its partial products at the
+  // end of the workspace (at most half of it) added in order into D; without
+  // room for two partials the product is one pass over the points, by few
+  // blocks and slower.  (hipBLASLt without a workspace is no alternative: its
+  // choice for 256 x 64 at k = 100,000 read out of range.)
   const size_t part = (size_t)g.m * g.n * sizeof(float);
-  if (g.transA && !g.transB && g.td == 0 && g.beta == 0.f && !g.bias && !g.Cin &&
-      g.k >= kSplitMinK && part <= kSplitMaxOut && g.ws) {
+  const bool wgrad_form = g.transA && !g.transB && g.td == 0 && g.beta == 0.f && !g.bias && !g.Cin;
+  if (wgrad_form && g.ta == g.tb && wgrad_served(g.m, g.n, g.k, g.ta)) {
+    const int64_t want = wgrad_splits(g.m, g.n, g.k, g.ta);
+    const int64_t most = g.ws ? (int64_t)(g.ws_bytes / 2 / part) : 0;
+    const int P = (int)(want <= most ? want : most > 1 ? most : 1);
+    float* parts = reinterpret_cast<float*>(g.D);
+    if (P > 1)
+      parts = reinterpret_cast<float*>(((uintptr_t)g.ws + g.ws_bytes - P * part) &
+                                       ~(uintptr_t)255);
+    if (launch_wgrad(g.m, g.n, g.k, g.alpha, g.A, g.B, g.ta, parts, P, st) != hipSuccess)
+      return (int)HIPBLAS_STATUS_EXECUTION_FAILED;
+    if (P == 1) return 0;
+    Segments seg{};
+    seg.dst[0] = reinterpret_cast<float*>(g.D);
+    seg.len[0] = g.m * g.n;
+    seg.n = 1;
+    return launch_reduce(parts, P, g.m * g.n, seg, st) == hipSuccess
+               ? 0 : (int)HIPBLAS_STATUS_EXECUTION_FAILED;
+  }
+  // Other long reductions into a small fp32 output (outputs that are no whole
+  // tiles, fp32 from 2^17 points, mixed types) are split over K: S
+  // strided-batched products of kc rows each (plus one for the rest) write S
+  // fp32 partials at the end of the workspace, added in order into D by the
+  // ordered reduction (deterministic; the whole GPU works on S times as many
+  // output tiles).
+  if (wgrad_form && g.k >= kSplitMinK && part <= kSplitMaxOut && g.ws) {
     int S = (int)(g.k / kSplitRows);
     S = S < kSplitMax ? S : kSplitMax;
     while (S >= 2 && (size_t)(S + 1) * part > g.ws_bytes / 2) --S;

@@ -278,6 +278,13 @@ struct HeadSumBatch {
 hipError_t launch_heads_sum_batch(int H, const HeadSumBatch& b, hipStream_t st);
 hipError_t launch_heads_sum(int H, int64_t L, int blockdiag, const float* src, float* dst,
                             hipStream_t st);
+// Weight gradients (pa_wgrad.hip): out [P][m][n] fp32, split p's part of
+// alpha A^T B over its range of the k rows (A [k,m], B [k,n], both in dtype;
+// the sum over p is the product; P = 1: the product itself).
+bool wgrad_served(int64_t m, int64_t n, int64_t k, int dtype);
+int wgrad_splits(int64_t m, int64_t n, int64_t k, int dtype);
+hipError_t launch_wgrad(int64_t m, int64_t n, int64_t k, float alpha, const void* A,
+                        const void* B, int dtype, float* out, int P, hipStream_t st);
 // Row-major D[m,n] = alpha op(A) op(B) + beta D (+ bias[n]) on hipBLASLt;
 // dtypes 0 fp32, 1 bf16.  Returns 0 or a hipblasStatus_t.
 struct Gemm {

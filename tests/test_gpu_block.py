@@ -186,6 +186,35 @@ def test_gemm(case):
               TOL[to] if to == "bf16" else 1e-5)
 
 
+# the weight-gradient kernel: every tile edge (64, 128, 256 where long enough),
+# ragged last steps (k mod 32), a single step per split, and a workspace too
+# small for all partials
+WGRADS = [  # m, n, k, dtype, workspace bytes
+    (64, 64, 512, "bf16", 1 << 24), (64, 128, 545, "f32", 1 << 24),
+    (128, 64, 1025, "f32", 1 << 24), (192, 320, 2047, "bf16", 1 << 24),
+    (128, 128, 4097, "f32", 1 << 24), (64, 64, 131071, "f32", 1 << 24),
+    (256, 1024, 4096, "bf16", 1 << 26), (256, 1024, 16385, "f32", 1 << 26),
+    (256, 256, 98305, "bf16", 1 << 26), (256, 128, 98337, "bf16", 1 << 24),
+    (64, 256, 98333, "bf16", 1 << 24), (128, 256, 100001, "bf16", 1 << 22),
+    (512, 128, 3333, "bf16", 0), (256, 64, 100000, "bf16", 0),
+]
+
+
+@pytest.mark.parametrize("case", WGRADS, ids=["x".join(map(str, c)) for c in WGRADS])
+def test_weight_gradient(case):
+    """D = alpha A^T B into a small output against float64: products of bf16
+    values are exact in fp32, so the error is the fp32 sums' alone (1e-5).
+    The workspace and D start as NaN: everything read is written first."""
+    import torch
+    m, n, k, dt, wsb = case
+    say(f"weight gradient {case}")
+    A, Bm = _rnd(dt, k, m, seed=31), _rnd(dt, k, n, seed=32, shift=0.5)
+    D = torch.full((m, n), float("nan"), device="cuda")
+    ws = torch.full((wsb,), 0xff, dtype=torch.uint8, device="cuda") if wsb else None
+    B.pa_gemm(dev(A, dt), dev(Bm, dt), D, transA=True, alpha=0.5, ws=ws)
+    check("D", host(D), 0.5 * (A.astype(np.float64).T @ Bm.astype(np.float64)), 1e-5)
+
+
 def test_colsum():
     import torch
     for dt, (N, C) in (("f32", (5003, 96)), ("bf16", (3001, 1024))):
