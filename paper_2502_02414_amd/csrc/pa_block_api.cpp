@@ -222,7 +222,7 @@ static pa_status mlp_up(const char* who, int64_t N, int K, int F, const void* X,
   }
   const size_t need_ws = (size_t)2 * F * K;
   if (ws_bytes < need_ws) return err(PA_ERR_WORKSPACE, "%s: workspace needs %zu bytes", who, need_ws);
-  PB_HIP(pa::launch_mlp_up(N, K, F, X, W1, b1, dY, W2, out, ws, as_stream(stream)), who);
+  PB_HIP(pa::launch_mlp_up(N, K, F, X, W1, b1, dY, W2, out, as_stream(stream)), who);
   return PA_OK;
 }
 

@@ -13,15 +13,32 @@
 // on v_mfma_f32_16x16x32_bf16 with fp32 accumulation; the activation is
 // applied to the fp32 accumulator and rounded to bf16 once.
 //
-// A block of four waves (eight in the backward, whose two products double
-// the weights staged per chunk) takes 32 points per wave (two 16-point MFMA
-// tiles) and walks the F = 4C output columns in chunks of FC: each chunk of
-// the weights ([F, K] rows: W1 transposed, or W2 as it is) is staged in LDS
-// once for the block, with the next chunk's loads in flight in registers;
-// each wave keeps its points' K-long rows of h (and dY) in registers as the
-// MFMA B operand for the whole column walk; results go through a
-// wave-private LDS staging tile so that every global store is a 16-byte,
-// row-contiguous access.
+// A block is persistent on its CU: each of its eight waves keeps the weights
+// of 16 NCT output columns in registers (the MFMA A operand; W1 transposed
+// once through LDS), and the block walks a range of the points in tiles of 32.
+// A tile's rows of h (and dY) come from HBM in whole rows, two tiles ahead,
+// through a double-buffered LDS tile that all eight waves read as the B
+// operand; the results leave through a triple-buffered LDS tile as whole rows
+// of the block's 128 NCT columns, so a tile costs one block barrier.  The
+// activation of one 16-point half is issued step by step beside the products of
+// the next.  The F / (128 NCT) column blocks of one range of points are placed on
+// one XCD, so that h and dY come from HBM once and from that XCD's L2 after
+// that.
+// Measured at N = 500,000, K = 256, F = 1024 (one box): forward 503 -> 389 us,
+// backward 761 -> 650 us; N = 4,000 46 -> 13 and 85 -> 15 us; K = 128 219 ->
+// 166 and 305 -> 237 us.  (Before: weights staged chunk by chunk by every
+// block of 128 or 256 points, two barriers a chunk, and a rational erf.)
+// What bounds it now, from copies of the kernel with parts removed: backward
+// 690 us of events, without stores 612, without the activation 597, without
+// its loads 621, with only loads and LDS traffic 372; LDS (20 GB at 128 bytes
+// a clock and CU: 290 us), the matrix cores (240 us), the VALU (280 us) and
+// HBM (300 us) are about equally loaded and overlap in part.  Also tried:
+// weights in LDS and the rows read from global memory as B operands (422 and
+// 708 us: 16 bytes per lane 512 bytes apart), the same with four waves of
+// twice the points (490 and 760 us), deeper LDS prefetch and scheduling groups
+// of MFMAs and VALU (no change).
+#include <type_traits>
+
 #include "pa_internal.h"
 #include "pa_stream.hpp"
 
@@ -29,224 +46,294 @@ namespace pa {
 
 namespace {
 
-// Phi(x) and exp(-x^2 / 2) from the rational approximation of erf of
-// Abramowitz and Stegun (formula 7.1.26; absolute error below 1.5e-7):
-//   erf(z) = 1 - (a1 t + a2 t^2 + a3 t^3 + a4 t^4 + a5 t^5) exp(-z^2),
-//   t = 1 / (1 + p z),  z = |x| / sqrt(2) >= 0.
-// Phi(x) = (1 + erf(x / sqrt 2)) / 2 is then 1 - q for x >= 0 and q for
-// x < 0, q = (a1 t + ... + a5 t^5) exp(-x^2 / 2) / 2, with no cancellation
-// in the lower tail.  Far below bf16's rounding step, which is what the
-// results are stored in.
-struct Gauss {
-  float Phi, e;
-};
-__device__ __forceinline__ Gauss gauss(float x) {
-  const float z = fabsf(x) * 0.70710678118654752f;
-  const float t = fast_rcp(fmaf(0.3275911f, z, 1.f));
-  float p = fmaf(t, 0.5f * 1.061405429f, 0.5f * -1.453152027f);
-  p = fmaf(t, p, 0.5f * 1.421413741f);
-  p = fmaf(t, p, 0.5f * -0.284496736f);
-  p = fmaf(t, p, 0.5f * 0.254829592f);
-  p *= t;
-  const float e = fast_exp2(-kLog2e * z * z);
-  const float q = p * e;
-  return {x >= 0.f ? 1.f - q : q, e};
+// GELU(x) = x Phi(x) = max(x, 0) - z Q(z) and GELU'(x) = Phi(x) + x phi(x),
+// z = |x|, Q(z) = 1 - Phi(z) the upper tail, phi(z) = exp(-z^2 / 2) /
+// sqrt(2 pi).  The activation is the bulk of the kernel's VALU work (a
+// transcendental takes the time of four other instructions), so each uses one
+// exp2 and a polynomial; both were fitted for this kernel (weighted minimax,
+// linear programming over 2,000 points):
+//   log2 Q(z) as a polynomial of degree 7 on [0, 13] (Q decays like
+//     exp(-z^2 / 2), so its logarithm is smooth): error of z Q(z) at most
+//     1.7e-7, and relative to Q at most 8e-4 up to z = 5 (evaluated in fp32);
+//   Q(z) - z phi(z) = (z0 - z) exp2(p(z)), z0 its only root, p of degree 8 on
+//     [0, 13]: error at most 1.6e-7, relative at most 7e-4 for 2 < z < 5;
+//     GELU'(x) is then 1/2 + sign(x) (1/2 - (Q - z phi)).
+// Both are far below bf16's rounding step, which is what the results are
+// stored in.  (The rational erf of Abramowitz and Stegun 7.1.26, evaluated
+// the same way: 2.1e-7 and 1.7e-7, with a reciprocal more.)  The
+// clamp keeps the polynomials finite and propagates NaN (IEEE minimum);
+// GELU(+inf) = inf, GELU(-inf) = 0 (to 1e-33).
+__device__ __forceinline__ float gelu_ap(float x) {
+  const float z = __builtin_elementwise_minimum(fabsf(x), 13.f);
+  float p = -4.718395132385922e-07f;
+  p = fmaf(p, z, 3.7946945667499676e-05f);
+  p = fmaf(p, z, -0.0007799809100106359f);
+  p = fmaf(p, z, 0.008062046952545643f);
+  p = fmaf(p, z, -0.05331820994615555f);
+  p = fmaf(p, z, -0.4588843584060669f);
+  p = fmaf(p, z, -1.1511520147323608f);
+  p = fmaf(p, z, -0.999998927116394f);
+  return fmaf(-z, fast_exp2(p), __builtin_elementwise_maximum(x, 0.f));
 }
-// GELU(x) = x Phi(x); GELU'(x) = Phi(x) + x phi(x), phi(x) = exp(-x^2/2) / sqrt(2 pi).
-__device__ __forceinline__ float gelu_ap(float x) { return x * gauss(x).Phi; }
 __device__ __forceinline__ float dgelu_ap(float x) {
-  const Gauss g = gauss(x);
-  return fmaf(x * 0.3989422804014327f, g.e, g.Phi);
+  const float z = __builtin_elementwise_minimum(fabsf(x), 13.f);
+  float p = 9.472704505242291e-07f;
+  p = fmaf(p, z, -3.0266723115346394e-05f);
+  p = fmaf(p, z, 0.0003959344467148185f);
+  p = fmaf(p, z, -0.0029573675710707903f);
+  p = fmaf(p, z, 0.014786088839173317f);
+  p = fmaf(p, z, -0.0547993965446949f);
+  p = fmaf(p, z, -0.560700535774231f);
+  p = fmaf(p, z, -0.38318517804145813f);
+  p = fmaf(p, z, -0.5884048342704773f);
+  const float h = fmaf(z - 0.7517915246935645f, fast_exp2(p), 0.5f);
+  return 0.5f + __builtin_copysignf(h, x);
 }
 
-#ifndef PA_MLP_WPAD
-#define PA_MLP_WPAD 32
-#endif
-
-template <int K, int FC, int PT, int NW, bool BWD>
+// NCT 16-column tiles per wave.
+template <int K, int NCT, bool BWD>
 struct MlpGeo {
-  static constexpr int WAVES = NW;
-  static constexpr int PW = 16 * PT;           // points per wave (PT 16-point MFMA tiles)
-  static constexpr int PTS = PW * WAVES;       // points per block
-  static constexpr int NM = BWD ? 2 : 1;       // weight matrices per chunk
-  static constexpr int WROW = K * 2 + PA_MLP_WPAD;  // chunk row in LDS (bytes, padded)
-  static constexpr int WMAT = FC * WROW;       // one matrix's chunk
-  static constexpr int SROW = FC * 2 + 16;     // staging row (bytes)
-  static constexpr int OFF_S = NM * WMAT;      // staging tiles, one per wave
-  static constexpr int SWAVE = PW * SROW;
-  static constexpr int LDS = OFF_S + WAVES * SWAVE;
-  static constexpr int RCH = K * 2 / 16;       // 16-byte chunks of a weight row
-  static constexpr int MCH = FC * RCH;         // ... of one matrix's chunk
-  static constexpr int WCH = NM * MCH / (64 * WAVES);  // per thread
-  static constexpr int KS = K / 32;            // K32 steps
-  static constexpr int CT = FC / 16;           // 16-column tiles per chunk
-  static constexpr int OCH = FC * 2 / 16;      // 16-byte chunks of a staged row
-  static_assert(NM * MCH == WCH * 64 * WAVES, "weight chunk must split evenly over the block");
-  static_assert(PW * OCH % 64 == 0, "staged rows must split evenly over a wave");
+  static constexpr int FCB = 128 * NCT;         // columns per block
+  static constexpr int PTS = 32;                // points per tile (two halves of 16)
+  static constexpr int KS = K / 32;             // K32 steps
+  static constexpr int XR = K * 2 + 32;         // LDS row of h, dY (padded)
+  static constexpr int XB = PTS * XR;
+  static constexpr int SR = FCB * 2 + 16;       // LDS row of the results
+  static constexpr int SB = PTS * SR;
+  static constexpr int OFF_Y = 2 * XB;
+  static constexpr int OFF_S = (BWD ? 4 : 2) * XB;
+  static constexpr int R1 = FCB * 2 + 32;       // row of a 32-channel slab of W1 (at the start)
+  static constexpr int USED = OFF_S + 3 * SB;
+  static constexpr int LDS = USED > 32 * R1 ? USED : 32 * R1;
+  static constexpr int XQ = PTS * K / 8;        // 16-byte chunks of an h tile
+  static constexpr int XN = (XQ + 511) / 512;   // ... per thread
+  static constexpr int SQ = PTS * FCB / 8 / 512;   // chunks of a result tile per thread
+  static constexpr int WQ = 32 * FCB / 8 / 512;    // chunks of a W1 slab per thread
+  static_assert(LDS <= kLdsBytes, "one block per CU fits");
 };
 
 struct MlpArgs {
   int64_t N;
   int F;
+  int PG;           // ranges of the points
   const bf16* X;    // [N, K]: h
   const bf16* DY;   // [N, K]: the MLP output's gradient (backward)
-  const bf16* W1T;  // [F, K]: W1 transposed
+  const bf16* W1;   // [K, F]
   const bf16* W2;   // [F, K] (backward)
   const float* b1;  // [F]
   bf16* out;        // [N, F]: GELU(u), or dU
 };
 
-template <int K, int FC, int PT, int NW, bool BWD>
-__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2)))
-k_mlp_up(MlpArgs a) {
-  using Gm = MlpGeo<K, FC, PT, NW, BWD>;
+template <int K, int NCT, bool BWD>
+__global__ void __launch_bounds__(512) k_mlp_up(MlpArgs a) {
+  using Gm = MlpGeo<K, NCT, BWD>;
+  constexpr int KS = Gm::KS, FCB = Gm::FCB, PTS = Gm::PTS;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int wave = threadIdx.x >> 6, lane = lane_id(), r = lane & 15, g = lane >> 4;
-  const int64_t n0 = (int64_t)blockIdx.x * Gm::PTS + Gm::PW * wave;  // the wave's first point
-  const int F = a.F, nch = F / FC;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = lane_id(), r = lane & 15, g = lane >> 4;
+  const int F = a.F, ncg = (F + FCB - 1) / FCB;
+  // blocks are dealt to the XCDs round robin: block b takes item l, so that
+  // the column blocks of one range of points share an XCD's L2
+  const int nb = gridDim.x, bl = blockIdx.x;
+  const int l = nb % 8 == 0 ? (bl % 8) * (nb / 8) + bl / 8 : bl;
+  const int pg = l / ncg, f0 = (l - pg * ncg) * FCB;
+  const int64_t tiles = (a.N + PTS - 1) / PTS;
+  const int64_t t0 = tiles * pg / a.PG, t1 = tiles * (pg + 1) / a.PG;  // t0 < t1 (PG <= tiles)
+  const int fw = f0 + 16 * NCT * wave;  // the wave's first column
+  const bool on = fw < F;               // (F a multiple of 64; NCT <= 4 divides the waves' share)
 
-  // the weight chunk of columns [c FC, c FC + FC): matrix m's rows, 16
-  // bytes per load, this thread's WCH of them
-  auto wsrc = [&](int e) {
-    const int m = Gm::NM == 2 ? e / Gm::MCH : 0;
-    const int q = e - m * Gm::MCH, row = q / Gm::RCH, cc = q - row * Gm::RCH;
-    return std::pair<int, int>(m, row * Gm::RCH + cc);
+  // the rows of tile t, 16-byte chunks q < XQ (past the end: the last one
+  // again); rows past N read row N - 1, their results are not stored
+  uint4 xr[Gm::XN], yr[BWD ? Gm::XN : 1];
+  auto chunk = [&](int j) {
+    const int q = threadIdx.x + 512 * j;
+    return Gm::XQ % 512 == 0 || q < Gm::XQ ? q : Gm::XQ - 1;
   };
-  uint4 wpre[Gm::WCH];
-  auto wload = [&](int c) {
+  auto load = [&](int64_t t) {
+    const int64_t p0 = (t < t1 ? t : t1 - 1) * PTS;
+    const int lim = last_row<PTS>(p0, a.N);
+    const char* xs = reinterpret_cast<const char*>(a.X + p0 * K);
+    const char* ys = BWD ? reinterpret_cast<const char*>(a.DY + p0 * K) : nullptr;
 #pragma unroll
-    for (int j = 0; j < Gm::WCH; ++j) {
-      const int e = threadIdx.x + 64 * NW * j;
-      const auto mq = wsrc(e);
-      const bf16* W = mq.first ? a.W2 : a.W1T;
-      wpre[j] = ld_global16<false>(reinterpret_cast<const char*>(W + (int64_t)c * FC * K) +
-                                   16 * mq.second);
+    for (int j = 0; j < Gm::XN; ++j) {
+      const int q = chunk(j), row = q / (K / 8), c = q % (K / 8);
+      const uint32_t off = (uint32_t)((row < lim ? row : lim) * K * 2 + 16 * c);
+      xr[j] = ld_global16<false>(xs + off);
+      if constexpr (BWD) yr[j] = ld_global16<false>(ys + off);
     }
   };
-  auto wstore = [&]() {
+  auto store = [&](int buf) {
 #pragma unroll
-    for (int j = 0; j < Gm::WCH; ++j) {
-      const int e = threadIdx.x + 64 * NW * j;
-      const auto mq = wsrc(e);
-      const int row = mq.second / Gm::RCH, cc = mq.second - row * Gm::RCH;
-      *reinterpret_cast<uint4*>(smem + mq.first * Gm::WMAT + row * Gm::WROW + 16 * cc) = wpre[j];
+    for (int j = 0; j < Gm::XN; ++j) {
+      const int q = chunk(j), row = q / (K / 8), c = q % (K / 8);
+      char* d = smem + buf * Gm::XB + row * Gm::XR + 16 * c;
+      *reinterpret_cast<uint4*>(d) = xr[j];
+      if constexpr (BWD) *reinterpret_cast<uint4*>(d + Gm::OFF_Y) = yr[j];
     }
   };
 
-  // the wave's rows of h (and dY) as MFMA B fragments: lane (r, g) holds
-  // row n0 + 16 pt + r, channels 32 s + 8 g .. + 7 (rows past N read row
-  // N - 1; their results are not stored)
-  K32<bf16> xf[PT][Gm::KS], yf[BWD ? PT : 1][BWD ? Gm::KS : 1];
+  // the wave's weights: lane (r, g) holds column fw + 16 ct + r, channels
+  // 32 s + 8 g .. + 7.  W1 [K, F] comes in slabs of 32 channels through LDS.
+  K32<bf16> w1[NCT][KS], w2[BWD ? NCT : 1][BWD ? KS : 1];
+  f32x4 bias[NCT];
+  {
+    uint4 v[KS][Gm::WQ];
 #pragma unroll
-  for (int pt = 0; pt < PT; ++pt) {
-    const int64_t n = n0 + 16 * pt + r;
-    const int64_t nn = n < a.N ? n : a.N - 1;
+    for (int s = 0; s < KS; ++s)
 #pragma unroll
-    for (int s = 0; s < Gm::KS; ++s) {
-      const uint32_t off = (uint32_t)(32 * s + 8 * g) * 2;
-      xf[pt][s].v = __builtin_bit_cast(
-          bf16x8, ld_global16<true>(reinterpret_cast<const char*>(a.X + nn * K) + off));
-      if constexpr (BWD)
-        yf[pt][s].v = __builtin_bit_cast(
-            bf16x8, ld_global16<true>(reinterpret_cast<const char*>(a.DY + nn * K) + off));
+      for (int j = 0; j < Gm::WQ; ++j) {
+        const int q = threadIdx.x + 512 * j, row = q / (FCB / 8), c = 8 * (q % (FCB / 8));
+        const int col = f0 + c < F ? f0 + c : F - 8;  // (columns past F are not stored)
+        v[s][j] = ld_global16<false>(a.W1 + (int64_t)(32 * s + row) * F + col);
+      }
+    const int tb = (8 * g + (r >> 2)) * Gm::R1 + 8 * (r & 3) + 32 * NCT * wave;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      block_sync();
+#pragma unroll
+      for (int j = 0; j < Gm::WQ; ++j) {
+        const int q = threadIdx.x + 512 * j, row = q / (FCB / 8), c = q % (FCB / 8);
+        *reinterpret_cast<uint4*>(smem + row * Gm::R1 + 16 * c) = v[s][j];
+      }
+      block_sync();
+#pragma unroll
+      for (int ct = 0; ct < NCT; ++ct) {
+        K16<bf16> lo, hi;
+        ld_tr<bf16>(lo, smem, tb, 32 * ct, Gm::R1);
+        ld_tr<bf16>(hi, smem, tb, 4 * Gm::R1 + 32 * ct, Gm::R1);
+        w1[ct][s].v = __builtin_shufflevector(lo.v, hi.v, 0, 1, 2, 3, 4, 5, 6, 7);
+      }
     }
   }
-  wload(0);
+  load(t0);
+#pragma unroll
+  for (int ct = 0; ct < NCT; ++ct) {
+    const int fc = on ? fw + 16 * ct : 0;
+    bias[ct] = *reinterpret_cast<const f32x4*>(a.b1 + fc + 4 * g);
+    if constexpr (BWD) {
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+        w2[ct][s].v = __builtin_bit_cast(
+            bf16x8, ld_global16<false>(a.W2 + (int64_t)(fc + r) * K + 32 * s + 8 * g));
+    }
+  }
+  block_sync();  // the last slab is read: its LDS becomes the tiles
+  store(0);
+  load(t0 + 1);
 
-  char* stg = smem + Gm::OFF_S + wave * Gm::SWAVE;
-  for (int c = 0; c < nch; ++c) {
-    block_sync();  // every wave is done with chunk c - 1
-    wstore();
+  const int xb = r * Gm::XR + 16 * g;  // B fragment: row 16 u + r, channels 32 s + 8 g ..
+  const int sb = Gm::OFF_S + r * Gm::SR + (16 * NCT * wave + 4 * g) * 2;
+  f32x4 accu[2][NCT], acc[2][BWD ? NCT : 1];  // X W1 + b1 and dY W2^T of two halves
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct) {
+      accu[u][ct] = zero4();
+      if constexpr (BWD) acc[u][ct] = zero4();
+    }
+  // columns 16 ct + 4 g .. + 3 of a half's point r, element e = 4 ct + i
+  auto act = [&](int u, int e, bf16x4& o) {
+    const int ct = e / 4, i = e % 4;
+    if constexpr (BWD)
+      o[i] = (bf16)(acc[u][ct][i] * dgelu_ap(accu[u][ct][i]));
+    else
+      o[i] = (bf16)gelu_ap(accu[u][ct][i]);
+  };
+  // products of half U of the tile in buffer `buf`, beside the activation of
+  // the half before (its results to the staging rows at `out`)
+  constexpr int EPS = 4 * NCT / KS > 0 ? 4 * NCT / KS : 1;  // elements per K32 step
+  auto half = [&](auto UC, const char* buf, char* out) {
+    constexpr int U = decltype(UC)::value;
+    K32<bf16> xf[2], yf[2];
+    auto frag = [&](int s) {
+      ld_k32(xf[s % 2], buf + xb + 16 * U * Gm::XR + 64 * s);
+      if constexpr (BWD) ld_k32(yf[s % 2], buf + Gm::OFF_Y + xb + 16 * U * Gm::XR + 64 * s);
+    };
+    frag(0);
+    bf16x4 o{};
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      if (s + 1 < KS) frag(s + 1);
+#pragma unroll
+      for (int ct = 0; ct < NCT; ++ct) {
+        accu[U][ct] = mma32(w1[ct][s], xf[s % 2], s == 0 ? bias[ct] : accu[U][ct]);
+        if constexpr (BWD)
+          acc[U][ct] = mma32(w2[ct][s], yf[s % 2], s == 0 ? zero4() : acc[U][ct]);
+      }
+#pragma unroll
+      for (int e = s * EPS; e < (s + 1) * EPS && e < 4 * NCT; ++e) {
+        act(U ^ 1, e, o);
+        if (e % 4 == 3) *reinterpret_cast<bf16x4*>(out + 32 * (e / 4)) = o;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // whole rows of a staged tile to memory
+  auto write = [&](int64_t t, const char* stg) {
+    const int64_t p0 = t * PTS;
+#pragma unroll
+    for (int j = 0; j < Gm::SQ; ++j) {
+      const int q = threadIdx.x + 512 * j, row = q / (FCB / 8), c = q % (FCB / 8);
+      const uint4 v = *reinterpret_cast<const uint4*>(stg + row * Gm::SR + 16 * c);
+      if (p0 + row < a.N && f0 + 8 * c < F) st_global16(a.out + (p0 + row) * F + f0 + 8 * c, v);
+    }
+  };
+
+  // Iteration t: tile t + 1 to the other buffer (last read before this
+  // barrier), tile t + 2 requested, tile t - 2 written out (its second half
+  // was staged during iteration t - 1), tile t computed.
+  using H0 = std::integral_constant<int, 0>;
+  using H1 = std::integral_constant<int, 1>;
+  int sp = 2, sc = 0;  // staging buffers of tiles t - 1 and t; the third is tile t - 2's
+  for (int64_t t = t0; t < t1; ++t) {
+    const int buf = (int)(t - t0) & 1;
     block_sync();
-    wload(c + 1 < nch ? c + 1 : c);  // (the last chunk again: no branch around the loads)
-
-    // accumulators [column tile][point tile]: acc = X W1 (forward) or
-    // dY W2^T (backward); accu = X W1 (backward)
-    f32x4 acc[Gm::CT][PT], accu[BWD ? Gm::CT : 1][PT];
-#pragma unroll
-    for (int ct = 0; ct < Gm::CT; ++ct)
-#pragma unroll
-      for (int pt = 0; pt < PT; ++pt) {
-        acc[ct][pt] = zero4();
-        if constexpr (BWD) accu[ct][pt] = zero4();
-      }
-#pragma unroll
-    for (int s = 0; s < Gm::KS; ++s) {
-#pragma unroll
-      for (int ct = 0; ct < Gm::CT; ++ct) {
-        const int ro = (16 * ct + r) * Gm::WROW + 64 * s + 16 * g;
-        K32<bf16> w1;
-        ld_k32(w1, smem + ro);
-        if constexpr (BWD) {
-          K32<bf16> w2;
-          ld_k32(w2, smem + Gm::WMAT + ro);
-#pragma unroll
-          for (int pt = 0; pt < PT; ++pt) {
-            acc[ct][pt] = mma32(w2, yf[pt][s], acc[ct][pt]);
-            accu[ct][pt] = mma32(w1, xf[pt][s], accu[ct][pt]);
-          }
-        } else {
-#pragma unroll
-          for (int pt = 0; pt < PT; ++pt) acc[ct][pt] = mma32(w1, xf[pt][s], acc[ct][pt]);
-        }
-      }
+    if (t + 1 < t1) store(buf ^ 1);
+    load(t + 2);
+    const int sn = 3 - sp - sc;
+    if (t >= t0 + 2) write(t - 2, smem + Gm::OFF_S + sn * Gm::SB);
+    if (on) {
+      // (the first tile's turn stages zeros where nothing is read)
+      half(H0{}, smem + buf * Gm::XB, smem + sb + sp * Gm::SB + 16 * Gm::SR);
+      half(H1{}, smem + buf * Gm::XB, smem + sb + sc * Gm::SB);
     }
-
-    // epilogue: lane (r, g) holds column c FC + 16 ct + 4 g + i of point
-    // n0 + 16 pt + r; staged as bf16 rows of the wave's points
+    sp = sc;
+    sc = sn;
+  }
+  if (on) {
+    bf16x4 o{};
 #pragma unroll
-    for (int ct = 0; ct < Gm::CT; ++ct) {
-      const f32x4 bias = *reinterpret_cast<const f32x4*>(a.b1 + c * FC + 16 * ct + 4 * g);
-#pragma unroll
-      for (int pt = 0; pt < PT; ++pt) {
-        bf16x4 o;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          if constexpr (BWD)
-            o[i] = (bf16)(acc[ct][pt][i] * dgelu_ap(accu[ct][pt][i] + bias[i]));
-          else
-            o[i] = (bf16)gelu_ap(acc[ct][pt][i] + bias[i]);
-        }
-        *reinterpret_cast<bf16x4*>(stg + (16 * pt + r) * Gm::SROW + (16 * ct + 4 * g) * 2) = o;
-      }
-    }
-    wave_sync();
-    // the staged rows to memory: 16-byte row-contiguous stores
-#pragma unroll
-    for (int j = 0; j < Gm::PW * Gm::OCH / 64; ++j) {
-      const int q = lane + 64 * j, row = q / Gm::OCH, cc = q - row * Gm::OCH;
-      const uint4 v = *reinterpret_cast<const uint4*>(stg + row * Gm::SROW + 16 * cc);
-      const int64_t n = n0 + row;
-      if (n < a.N)
-        st_global16(reinterpret_cast<char*>(a.out + n * F + (int64_t)c * FC) + 16 * cc, v);
+    for (int e = 0; e < 4 * NCT; ++e) {
+      act(1, e, o);
+      if (e % 4 == 3)
+        *reinterpret_cast<bf16x4*>(smem + sb + sp * Gm::SB + 16 * Gm::SR + 32 * (e / 4)) = o;
     }
   }
+  block_sync();
+  if (t1 - t0 >= 2) write(t1 - 2, smem + Gm::OFF_S + (3 - sp - sc) * Gm::SB);
+  write(t1 - 1, smem + Gm::OFF_S + sp * Gm::SB);
 }
 
-// W [K, F] -> WT [F, K] (bf16), 32 x 32 tiles through LDS.
-__global__ void __launch_bounds__(256) k_transpose_bf16(int K, int F, const bf16* W, bf16* WT) {
-  __shared__ bf16 t[32][33];
-  const int f0 = blockIdx.x * 32, k0 = blockIdx.y * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  for (int y = ty; y < 32; y += 8) {
-    const int k = k0 + y, f = f0 + tx;
-    t[y][tx] = (k < K && f < F) ? W[(int64_t)k * F + f] : (bf16)0.f;
-  }
-  __syncthreads();
-  for (int y = ty; y < 32; y += 8) {
-    const int f = f0 + y, k = k0 + tx;
-    if (f < F && k < K) WT[(int64_t)f * K + k] = t[tx][y];
-  }
-}
-
-template <int K, int FC, int PT, int NW, bool BWD>
-hipError_t launch_k(const MlpArgs& a, hipStream_t st) {
-  using Gm = MlpGeo<K, FC, PT, NW, BWD>;
-  const int64_t blocks = (a.N + Gm::PTS - 1) / Gm::PTS;
-  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_mlp_up<K, FC, PT, NW, BWD>), dim3((unsigned)blocks), dim3(64 * NW),
-                     Gm::LDS, st, a);
+// One block per CU (256), or fewer where there are not as many tiles.
+template <int K, int NCT, bool BWD>
+hipError_t launch_k(MlpArgs a, hipStream_t st) {
+  using Gm = MlpGeo<K, NCT, BWD>;
+  const int64_t tiles = (a.N + Gm::PTS - 1) / Gm::PTS;
+  const int ncg = (a.F + Gm::FCB - 1) / Gm::FCB;
+  const int64_t PG = ncg < 256 ? 256 / ncg : 1;
+  a.PG = (int)(PG < tiles ? PG : tiles);
+  hipLaunchKernelGGL((k_mlp_up<K, NCT, BWD>), dim3(ncg * a.PG), dim3(512), Gm::LDS, st, a);
   return hipGetLastError();
+}
+// Columns per wave: 64 forward and 32 backward (two weight matrices) fill
+// half of a wave's registers at K = 256 and read h the fewest times; fewer
+// where F is no multiple of the block's columns (idle waves).
+template <int K>
+hipError_t launch_kf(const MlpArgs& a, hipStream_t st) {
+  if (a.DY) return a.F % 256 == 0 ? launch_k<K, 2, true>(a, st) : launch_k<K, 1, true>(a, st);
+  return a.F % 512 == 0   ? launch_k<K, 4, false>(a, st)
+         : a.F % 256 == 0 ? launch_k<K, 2, false>(a, st)
+                          : launch_k<K, 1, false>(a, st);
 }
 
 }  // namespace
@@ -256,20 +343,15 @@ bool mlp_up_served(int K, int F) {
 }
 
 hipError_t launch_mlp_up(int64_t N, int K, int F, const void* X, const void* W1, const float* b1,
-                         const void* DY, const void* W2, void* out, void* W1T, hipStream_t st) {
-  if (N < 1 || !mlp_up_served(K, F) || !X || !W1 || !b1 || !out || !W1T) return hipErrorInvalidValue;
+                         const void* DY, const void* W2, void* out, hipStream_t st) {
+  if (N < 1 || !mlp_up_served(K, F) || !X || !W1 || !b1 || !out) return hipErrorInvalidValue;
   if (DY && !W2) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_transpose_bf16, dim3((F + 31) / 32, (K + 31) / 32), dim3(256), 0, st, K, F,
-                     (const bf16*)W1, (bf16*)W1T);
-  MlpArgs a{N, F, (const bf16*)X, (const bf16*)DY, (const bf16*)W1T, (const bf16*)W2, b1,
+  MlpArgs a{N, F, 1, (const bf16*)X, (const bf16*)DY, (const bf16*)W1, (const bf16*)W2, b1,
             (bf16*)out};
-  const bool bwd = DY != nullptr;
   switch (K) {
-    case 64: return bwd ? launch_k<64, 32, 2, 8, true>(a, st) : launch_k<64, 64, 2, 4, false>(a, st);
-    case 128:
-      return bwd ? launch_k<128, 32, 2, 8, true>(a, st) : launch_k<128, 64, 2, 4, false>(a, st);
-    default:
-      return bwd ? launch_k<256, 32, 2, 8, true>(a, st) : launch_k<256, 64, 2, 4, false>(a, st);
+    case 64: return launch_kf<64>(a, st);
+    case 128: return launch_kf<128>(a, st);
+    default: return launch_kf<256>(a, st);
   }
 }
 

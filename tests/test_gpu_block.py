@@ -148,6 +148,41 @@ def test_mlp_up(case):
         assert err.max() < 2e-2, (name, err.max())
 
 
+# tile edges (32 points, halves of 16), several tiles per block, columns that
+# leave waves idle, every number of columns per wave
+MLP_EDGES = [(31, 64, 64), (33, 64, 192), (97, 128, 320), (16385, 128, 256), (65, 256, 128),
+             (20011, 256, 512), (8225, 256, 1024)]
+
+
+@pytest.mark.parametrize("case", MLP_EDGES, ids=[f"N{c[0]}-K{c[1]}-F{c[2]}" for c in MLP_EDGES])
+def test_mlp_up_edges(case):
+    test_mlp_up(case)
+
+
+def test_mlp_up_non_finite():
+    """Pre-activations of +inf, -inf and NaN: GELU inf, 0, NaN; its slope 1, 0, NaN."""
+    import torch
+    N, K, F = 50, 64, 64
+    X, dY = _rnd("bf16", N, K, seed=25), _rnd("bf16", N, K, seed=26)
+    W1, W2 = _rnd("bf16", K, F, seed=27), _rnd("bf16", F, K, scale=F ** -0.5, seed=28)
+    b1 = _rnd("f32", F, seed=29)
+    b1[3], b1[17], b1[40], b1[50] = np.inf, -np.inf, np.nan, 1e20
+    ws = torch.empty(2 * F * K, dtype=torch.uint8, device="cuda")
+    G, dU = dev(np.zeros((N, F)), "bf16"), dev(np.zeros((N, F)), "bf16")
+    Xd, W1d, b1d = dev(X, "bf16"), dev(W1, "bf16"), dev(b1)
+    B.pa_mlp_up(Xd, W1d, b1d, G, ws)
+    B.pa_mlp_up_backward(Xd, W1d, b1d, dev(dY, "bf16"), dev(W2, "bf16"), dU, ws)
+    G, dU = host(G), host(dU)
+    dg = dY.astype(np.float64) @ W2.astype(np.float64).T
+    assert np.all(G[:, 3] == np.inf) and np.all(np.abs(G[:, 17]) < 1e-30)
+    assert np.all(np.isnan(G[:, 40])) and np.all(np.isnan(dU[:, 40]))
+    assert np.allclose(G[:, 50], 1e20, rtol=4e-3) and np.all(np.abs(dU[:, 17]) < 1e-30)
+    for j in (3, 50):
+        assert np.abs(dU[:, j] - dg[:, j]).max() < 2e-2 * np.abs(dg).max()
+    assert np.isfinite(np.delete(G, [3, 40], axis=1)).all()
+    assert np.isfinite(np.delete(dU, 40, axis=1)).all()
+
+
 GEMMS = [  # m, n, k, transA, transB, in dtype, out dtype, bias, residual
     (1000, 96, 64, False, False, "f32", "f32", True, False),
     (1000, 96, 64, False, True, "f32", "f32", False, True),
