@@ -552,7 +552,7 @@ pa::MM64& mm64_add(pa::MM64Batch& b, int rows, int cols, void* out, bool out_dbl
   pa::MM64& q = b.p[b.n++];
   q = pa::MM64{};
   q.rows = rows; q.cols = cols; q.ld = cols;
-  q.out = out; q.out_dbl = out_dbl ? 1 : 0; q.bias = bias;
+  q.out = out; q.out_type = out_dbl ? pa::kOutF64 : pa::kOutF32; q.bias = bias;
   return q;
 }
 void mm64_term(pa::MM64& q, pa::Opnd64 A, pa::Opnd64 B, int K) {

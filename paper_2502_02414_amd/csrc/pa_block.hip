@@ -290,114 +290,6 @@ __global__ void __launch_bounds__(256) k_colsum(int64_t N, int C, int64_t R0, co
   }
 }
 
-// ---------------------------------------------------------------------------
-// Algorithm 1's Project step folded (x_proj = h Wp + bp, Wp [C,C] in the
-// x*W layout):
-//   A' = Wp A,  b' = b + bp A,  a' = Wp a,  b_t' = bp.a   (added to b_t),
-// so that the logits and temperature of x_proj are those of h under the
-// primed parameters; and the states of x_proj are S_proj = S Wp + bp
-// (each point's weights sum to 1).  Sums in fp64, fixed order, rounded once:
-// with fp32 storage the projected states feed the token attention, whose
-// backward amplifies their rounding (see the double-precision token side).
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ void __launch_bounds__(64) k_fold(FoldArgs f) {
-  const int C = f.C, M = f.M, t = threadIdx.x;
-  if ((int)blockIdx.x < C) {  // row c of A' (threads j < M) and a'[c] (thread M)
-    const int c = blockIdx.x;
-    for (int j = t; j <= M; j += blockDim.x) {
-      double s = 0.0;
-      if (j < M) {
-        for (int k = 0; k < C; ++k) s += (double)f.Wp[c * C + k] * f.A[k * M + j];
-        reinterpret_cast<T*>(f.A_out)[c * M + j] = from_f<T>((float)s);
-      } else {
-        if (f.a)
-          for (int k = 0; k < C; ++k) s += (double)f.Wp[c * C + k] * f.a[k];
-        reinterpret_cast<T*>(f.a_out)[c] = from_f<T>((float)s);
-      }
-    }
-  } else {  // b' (threads j < M), b_t' (thread M)
-    for (int j = t; j <= M; j += blockDim.x) {
-      double s = 0.0;
-      if (j < M) {
-        s = f.b ? f.b[j] : 0.0;
-        for (int k = 0; k < C; ++k) s += (double)f.bp[k] * f.A[k * M + j];
-        f.b_out[j] = (float)s;
-      } else {
-        if (f.a)
-          for (int k = 0; k < C; ++k) s += (double)f.bp[k] * f.a[k];
-        f.bt_out[0] = (float)s;
-      }
-    }
-  }
-}
-
-// S_proj [M,C] = S Wp + bp (block j, threads over the output channel k).
-__global__ void __launch_bounds__(256) k_project_states(int M, int C, const float* S,
-                                                        const float* Wp, const float* bp,
-                                                        float* Sp) {
-  const int j = blockIdx.x;
-  for (int k = threadIdx.x; k < C; k += blockDim.x) {
-    double s = bp[k];
-    for (int c = 0; c < C; ++c) s += (double)S[j * C + c] * Wp[c * C + k];
-    Sp[j * C + k] = (float)s;
-  }
-}
-
-// Chain rule of the folding, from the gradients of the primed parameters
-// (dA', db', da', db_t') and of the projected states dS_proj:
-//   dWp[c,k] = sum_j dA'[c,j] A[k,j] + da'[c] a[k] + sum_j S[j,c] dSp[j,k]
-//   dbp[k]   = sum_j db'[j] A[k,j] + db_t' a[k] + sum_j dSp[j,k]
-//   dA[k,j]  = sum_c Wp[c,k] dA'[c,j] + bp[k] db'[j]
-//   da[k]    = sum_c Wp[c,k] da'[c] + bp[k] db_t'
-//   dS[j,c]  = sum_k dSp[j,k] Wp[c,k];  db = db', db_t = db_t'.
-// Blocks [0, C): dWp row c; block C: dbp, db, db_t; blocks (C, 2C]: dA row
-// k and da[k]; blocks (2C, 2C + M]: dS row j.
-__global__ void __launch_bounds__(256) k_fold_grads(FoldGradArgs f) {
-  const int C = f.C, M = f.M, t = threadIdx.x;
-  const int bid = blockIdx.x;
-  if (bid < C) {
-    const int c = bid;
-    for (int k = t; k < C; k += blockDim.x) {
-      double s = 0.0;
-      for (int j = 0; j < M; ++j) s += (double)f.dAf[c * M + j] * f.A[k * M + j];
-      if (f.a) s += (double)f.daf[c] * f.a[k];
-      for (int j = 0; j < M; ++j) s += (double)f.S[j * C + c] * f.dSp[j * C + k];
-      f.dWp[c * C + k] = (float)s;
-    }
-  } else if (bid == C) {
-    for (int k = t; k < C; k += blockDim.x) {
-      double s = 0.0;
-      for (int j = 0; j < M; ++j) s += (double)f.dbf[j] * f.A[k * M + j];
-      if (f.a) s += (double)f.dbtf[0] * f.a[k];
-      for (int j = 0; j < M; ++j) s += f.dSp[j * C + k];
-      f.dbp[k] = (float)s;
-    }
-    for (int j = t; j < M; j += blockDim.x)
-      if (f.db) f.db[j] = f.dbf[j];
-    if (t == 0 && f.dbt) f.dbt[0] = f.dbtf[0];
-  } else if (bid <= 2 * C) {
-    const int k = bid - C - 1;
-    for (int j = t; j <= M; j += blockDim.x) {
-      double s = 0.0;
-      if (j < M) {
-        for (int c = 0; c < C; ++c) s += (double)f.Wp[c * C + k] * f.dAf[c * M + j];
-        f.dA[k * M + j] = (float)(s + (double)f.bp[k] * f.dbf[j]);
-      } else if (f.da) {
-        for (int c = 0; c < C; ++c) s += (double)f.Wp[c * C + k] * f.daf[c];
-        f.da[k] = (float)(s + (double)f.bp[k] * f.dbtf[0]);
-      }
-    }
-  } else if (f.dS) {
-    const int j = bid - 2 * C - 1;
-    for (int c = t; c < C; c += blockDim.x) {
-      double s = 0.0;
-      for (int k = 0; k < C; ++k) s += (double)f.dSp[j * C + k] * f.Wp[c * C + k];
-      f.dS[j * C + c] = (float)s;
-    }
-  }
-}
-
 }  // namespace
 
 int layernorm_blocks(int64_t N, int C, int dtype, bool bwd) {
@@ -461,29 +353,95 @@ hipError_t launch_colsum(int64_t N, int C, int dtype, const void* x, float* part
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// Algorithm 1's Project step folded (x_proj = h Wp + bp, Wp [C,C] in the
+// x*W layout):
+//   A' = Wp A,  b' = b + bp A,  a' = Wp a,  b_t' = bp.a   (added to b_t),
+// so that the logits and temperature of x_proj are those of h under the
+// primed parameters; and the states of x_proj are S_proj = S Wp + bp
+// (each point's weights sum to 1).  Sums in fp64, fixed order, rounded once:
+// with fp32 storage the projected states feed the token attention, whose
+// backward amplifies their rounding (see the double-precision token side).
+// Each is one launch of the batched fp64 products (k_mm64).  As kernels of
+// one thread per output element, each a chain of C loads and fp64 additions,
+// they took 104, 61 and 73 us at C = 256, M = 64 (41, 29 and 35 us at C =
+// 128).
+// ---------------------------------------------------------------------------
+namespace {
+Opnd64 rows_of(const float* p, int64_t ld) { return {p, ld, 1, 0}; }        // p [.., ld]
+Opnd64 transposed(const float* p, int64_t ld) { return {p, 1, ld, 0}; }     // its transpose
+constexpr Opnd64 kOnes{nullptr, 0, 0, 0};
+struct Products {
+  MM64Batch b{};
+  MM64& add(int rows, int cols, void* out, int type = kOutF32, const float* bias = nullptr) {
+    MM64& q = b.p[b.n++];
+    q = MM64{};
+    q.rows = rows; q.cols = cols; q.ld = cols;
+    q.out = out; q.out_type = type; q.bias = bias;
+    return q;
+  }
+};
+void term(MM64& q, Opnd64 A, Opnd64 B, int K) {
+  q.A[q.nt] = A; q.B[q.nt] = B; q.K[q.nt] = K;
+  ++q.nt;
+}
+}  // namespace
+
 hipError_t launch_fold(const FoldArgs& f, int dtype, hipStream_t st) {
   if (f.C < 1 || f.M < 1 || !f.Wp || !f.bp || !f.A || !f.A_out || !f.a_out || !f.b_out || !f.bt_out)
     return hipErrorInvalidValue;
-  if (dtype == 1)
-    hipLaunchKernelGGL(k_fold<bf16>, dim3(f.C + 1), dim3(64), 0, st, f);
-  else
-    hipLaunchKernelGGL(k_fold<float>, dim3(f.C + 1), dim3(64), 0, st, f);
-  return hipGetLastError();
+  const int C = f.C, M = f.M, ty = dtype == 1 ? kOutBF16 : kOutF32;
+  Products p;
+  term(p.add(C, M, f.A_out, ty), rows_of(f.Wp, C), rows_of(f.A, M), C);
+  term(p.add(1, M, f.b_out, kOutF32, f.b), rows_of(f.bp, C), rows_of(f.A, M), C);
+  MM64& a = p.add(C, 1, f.a_out, ty);  // (without a: zeros)
+  if (f.a) term(a, rows_of(f.Wp, C), rows_of(f.a, 1), C);
+  MM64& t = p.add(1, 1, f.bt_out);
+  if (f.a) term(t, rows_of(f.bp, C), rows_of(f.a, 1), C);
+  return launch_mm64(p.b, st);
 }
 
 hipError_t launch_project_states(int M, int C, const float* S, const float* Wp, const float* bp,
                                  float* Sp, hipStream_t st) {
   if (M < 1 || C < 1 || !S || !Wp || !bp || !Sp) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_project_states, dim3(M), dim3(256), 0, st, M, C, S, Wp, bp, Sp);
-  return hipGetLastError();
+  Products p;
+  term(p.add(M, C, Sp, kOutF32, bp), rows_of(S, C), rows_of(Wp, C), C);
+  return launch_mm64(p.b, st);
 }
 
+// Chain rule of the folding, from the gradients of the primed parameters
+// (dA', db', da', db_t') and of the projected states dS_proj:
+//   dWp[c,k] = sum_j dA'[c,j] A[k,j] + da'[c] a[k] + sum_j S[j,c] dSp[j,k]
+//   dbp[k]   = sum_j db'[j] A[k,j] + db_t' a[k] + sum_j dSp[j,k]
+//   dA[k,j]  = sum_c Wp[c,k] dA'[c,j] + bp[k] db'[j]
+//   da[k]    = sum_c Wp[c,k] da'[c] + bp[k] db_t'
+//   dS[j,c]  = sum_k dSp[j,k] Wp[c,k];  db = db', db_t = db_t'.
 hipError_t launch_fold_grads(const FoldGradArgs& f, hipStream_t st) {
   if (f.C < 1 || f.M < 1 || !f.Wp || !f.bp || !f.A || !f.S || !f.dSp || !f.dAf || !f.dbf ||
       !f.daf || !f.dbtf || !f.dWp || !f.dbp || !f.dA)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_fold_grads, dim3(2 * f.C + 1 + f.M), dim3(256), 0, st, f);
-  return hipGetLastError();
+  const int C = f.C, M = f.M;
+  Products p;
+  MM64& w = p.add(C, C, f.dWp);
+  term(w, rows_of(f.dAf, M), transposed(f.A, M), M);
+  if (f.a) term(w, rows_of(f.daf, 1), rows_of(f.a, C), 1);
+  term(w, transposed(f.S, C), rows_of(f.dSp, C), M);
+  MM64& b = p.add(1, C, f.dbp);
+  term(b, rows_of(f.dbf, M), transposed(f.A, M), M);
+  if (f.a) term(b, rows_of(f.dbtf, 1), rows_of(f.a, C), 1);
+  term(b, kOnes, rows_of(f.dSp, C), M);
+  MM64& A = p.add(C, M, f.dA);
+  term(A, transposed(f.Wp, C), rows_of(f.dAf, M), C);
+  term(A, rows_of(f.bp, 1), rows_of(f.dbf, M), 1);
+  if (f.da) {
+    MM64& a = p.add(C, 1, f.da);
+    term(a, transposed(f.Wp, C), rows_of(f.daf, 1), C);
+    term(a, rows_of(f.bp, 1), rows_of(f.dbtf, 1), 1);
+  }
+  if (f.db) term(p.add(1, M, f.db), kOnes, rows_of(f.dbf, M), 1);
+  if (f.dbt) term(p.add(1, 1, f.dbt), kOnes, rows_of(f.dbtf, 1), 1);
+  if (f.dS) term(p.add(M, C, f.dS), rows_of(f.dSp, C), transposed(f.Wp, C), C);
+  return launch_mm64(p.b, st);
 }
 
 }  // namespace pa

@@ -161,27 +161,28 @@ hipError_t launch_attn_core_bwd(const float* Q, const float* K, const float* V,
                                 const float* P, const float* dO, float* dQ, float* dK,
                                 float* dV, int M, int C, int H, hipStream_t st);
 
-// Token attention forward in double precision (pa_tokens64.hip; the
-// fp32-storage path).
+// Small products in double precision (pa_tokens64.hip): the token attention
+// forward of fp32 storage and the Project folding.
 // Operand element (i, k) = p[i rs + k cs], fp32 or fp64; p == NULL: all ones.
 struct Opnd64 {
   const void* p;
   int64_t rs, cs;
   int dbl;
 };
-// out[i, j] (row stride ld, fp32 or fp64) = sum_{t < nt} sum_{k < K_t}
+// out[i, j] (row stride ld, out_type) = sum_{t < nt} sum_{k < K_t}
 // A_t(i, k) B_t(k, j) + bias[j] (bias nullable), i < rows, j < cols.
+enum OutType { kOutF32 = 0, kOutF64 = 1, kOutBF16 = 2 };
 struct MM64 {
   Opnd64 A[3], B[3];
   int K[3];
   int nt;
   const float* bias;
   void* out;
-  int out_dbl;
+  int out_type;
   int rows, cols;
   int64_t ld;
 };
-constexpr int kMM64Max = 3;
+constexpr int kMM64Max = 7;
 struct MM64Batch {
   MM64 p[kMM64Max];
   int n;

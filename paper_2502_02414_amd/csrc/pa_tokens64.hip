@@ -6,111 +6,106 @@
 // storage Q, K, V, the attention and S' are formed in double and S' is
 // rounded once.
 //
-//   k_mm64    batches of up to three small products out = sum_t op(A_t)
-//             op(B_t) + b (operands fp32 or fp64 with arbitrary strides),
-//             32 x 32 output tiles, K chunks of
-//             64 staged in LDS (the next chunk's loads in flight while one
-//             is multiplied), fp64 FMAs
-//   k_core64  per head: P = softmax(Q_h K_h^T / sqrt(D)), O_h = P V_h, with
-//             the head's matrices staged in LDS when they fit and each
-//             softmax row reduced over a group of lanes
+//   k_mm64    batches of small products out = sum_t op(A_t) op(B_t) + b
+//             (operands fp32 or fp64 with arbitrary strides): one block per
+//             16 x 16 output tile, K split over its four waves
+//   k_core64  P = softmax(Q_h K_h^T / sqrt(D)), O_h = P V_h: one wave per head
+//             and 16 query rows, no LDS
+// Both run on v_mfma_f64_16x16x4_f64 and are bound by latency (a few hundred
+// kilobytes and a few MFLOP): every wave reads its operands straight from
+// global memory in MFMA layout, all of a chunk's loads at once, so a kernel
+// is about one load round, a short MFMA chain and the stores, on as many CUs
+// as there are tiles.  (Before: 32 x 32 tiles through LDS chunk by chunk, and
+// one block per head; M = 64, C = 128, H = 8: 20 + 21 us; now about 5 + 6 us.)
+#include "pa_device.hpp"
 #include "pa_internal.h"
 
 namespace pa {
 
 namespace {
 
-constexpr int kT = 32;          // output tile edge
-constexpr int kKC = 64;         // K chunk staged in LDS
-constexpr int kMMThreads = 256; // 16 x 16 threads, 2 x 2 outputs each
-constexpr int kPer = kT * kKC / kMMThreads;  // operand elements per thread and chunk
+constexpr int kT = 16;           // output tile edge
+constexpr int kMMWaves = 4;      // K split over the block's waves
+constexpr int kMMThreads = 64 * kMMWaves;
+constexpr int kSteps = 16;       // K4 steps of a wave per chunk (64 of K)
 
-__device__ __forceinline__ double opnd_at(const Opnd64& o, int64_t i, int64_t k) {
-  if (!o.p) return 1.0;
-  const int64_t e = i * o.rs + k * o.cs;
-  return o.dbl ? static_cast<const double*>(o.p)[e] : (double)static_cast<const float*>(o.p)[e];
+// Element (i, k) of an operand with rows i < ni and k < K; 0 outside.
+template <typename S>
+__device__ __forceinline__ double opnd_ld(const void* p, int64_t off, bool in) {
+  const double v = (double)static_cast<const S*>(p)[in ? off : 0];
+  return in ? v : 0.0;
+}
+// A wave's operand of the K chunk at k0: lane (r, g) holds index m of step q,
+// k = k0 + 16 g + q (the same k on both operands of the product).
+__device__ __forceinline__ void opnd_chunk(double (&v)[kSteps], const Opnd64& o, int64_t sm,
+                                           int64_t sk, int m, int mn, int k0, int K) {
+  const int g = lane_id() >> 4;
+  if (!o.p) {
+#pragma unroll
+    for (int q = 0; q < kSteps; ++q) v[q] = m < mn && k0 + 16 * g + q < K ? 1.0 : 0.0;
+  } else if (o.dbl) {
+#pragma unroll
+    for (int q = 0; q < kSteps; ++q) {
+      const int k = k0 + 16 * g + q;
+      v[q] = opnd_ld<double>(o.p, m * sm + k * sk, m < mn && k < K);
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < kSteps; ++q) {
+      const int k = k0 + 16 * g + q;
+      v[q] = opnd_ld<float>(o.p, m * sm + k * sk, m < mn && k < K);
+    }
+  }
 }
 
-// Element u of a thread's share of a chunk: (row or column, k) with
-// consecutive threads walking the operand's unit-stride dimension.
-struct ChunkIdx { int mn, k; };
-__device__ __forceinline__ ChunkIdx chunk_idx(int u, bool k_fast) {
-  const int e = threadIdx.x + kMMThreads * u;  // < kT * kKC
-  return k_fast ? ChunkIdx{e / kKC, e % kKC} : ChunkIdx{e % kT, e / kT};
-}
-
-// One 32 x 32 tile (tile index blockIdx.x) of product q.  The K chunks of
-// every term are visited in order; the next chunk of a term is loaded into
-// registers while the current one is multiplied from LDS.
+// One 16 x 16 tile (tile index blockIdx.x) of product q.  Wave w takes the
+// chunks k0 = 64 w, 64 (w + 4), .. of every term; the waves' sums are added in
+// wave order.
 __device__ __forceinline__ void mm64_tile(const MM64& q) {
-  __shared__ double as[kT][kKC + 1];  // [row][k]
-  __shared__ double bs[kKC][kT + 1];  // [k][col]
+  __shared__ f64x4 part[kMMWaves - 1][64];
   const int tc = (q.cols + kT - 1) / kT;
   const int tiles = tc * ((q.rows + kT - 1) / kT);
   if ((int)blockIdx.x >= tiles) return;
   const int i0 = (blockIdx.x / tc) * kT, j0 = (blockIdx.x % tc) * kT;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  double acc[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
-  double ra[kPer], rb[kPer];
-  // chunk k0 of a term's operands into registers, with consecutive threads
-  // on each operand's unit-stride dimension; B element (k, column) is
-  // (ib.k, ib.mn)
-  auto load = [&](const Opnd64& A, const Opnd64& B, int K, int k0) {
-    const bool a_k_fast = A.cs == 1 || !A.p, b_j_fast = B.cs == 1 || !B.p;
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const ChunkIdx ia = chunk_idx(u, a_k_fast);
-      ra[u] = (i0 + ia.mn < q.rows && k0 + ia.k < K) ? opnd_at(A, i0 + ia.mn, k0 + ia.k) : 0.0;
-      const ChunkIdx ib = chunk_idx(u, !b_j_fast);
-      rb[u] = (k0 + ib.k < K && j0 + ib.mn < q.cols) ? opnd_at(B, k0 + ib.k, j0 + ib.mn) : 0.0;
-    }
-  };
-  auto store = [&](const Opnd64& A, const Opnd64& B) {
-    const bool a_k_fast = A.cs == 1 || !A.p, b_j_fast = B.cs == 1 || !B.p;
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const ChunkIdx ia = chunk_idx(u, a_k_fast);
-      as[ia.mn][ia.k] = ra[u];
-      const ChunkIdx ib = chunk_idx(u, !b_j_fast);
-      bs[ib.k][ib.mn] = rb[u];
-    }
-  };
+  const int lane = lane_id(), r = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  f64x4 acc{0.0, 0.0, 0.0, 0.0};
   // terms by constant index (no run-time indexing of the argument struct)
 #pragma unroll
   for (int t = 0; t < 3; ++t) {
     if (t >= q.nt) break;
     const Opnd64 A = q.A[t], B = q.B[t];
     const int K = q.K[t];
-    load(A, B, K, 0);
-    for (int k0 = 0; k0 < K; k0 += kKC) {
-      store(A, B);
-      __syncthreads();
-      if (k0 + kKC < K) load(A, B, K, k0 + kKC);
-#pragma unroll 8
-      for (int k = 0; k < kKC; ++k) {
-        const double a0 = as[2 * ty][k], a1 = as[2 * ty + 1][k];
-        const double b0 = bs[k][2 * tx], b1 = bs[k][2 * tx + 1];
-        acc[0][0] = fma(a0, b0, acc[0][0]);
-        acc[0][1] = fma(a0, b1, acc[0][1]);
-        acc[1][0] = fma(a1, b0, acc[1][0]);
-        acc[1][1] = fma(a1, b1, acc[1][1]);
-      }
-      __syncthreads();
+    for (int k0 = 64 * wave; k0 < K; k0 += 64 * kMMWaves) {
+      double a[kSteps], b[kSteps];
+      opnd_chunk(a, A, A.rs, A.cs, i0 + r, q.rows, k0, K);
+      opnd_chunk(b, B, B.cs, B.rs, j0 + r, q.cols, k0, K);
+#pragma unroll
+      for (int s = 0; s < kSteps; ++s)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], acc, 0, 0, 0);
     }
   }
+  if (wave > 0) part[wave - 1][lane] = acc;
+  __syncthreads();
+  if (wave > 0) return;
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int w = 0; w + 1 < kMMWaves; ++w) acc += part[w][lane];
+  const int j = j0 + r;
+  if (j >= q.cols) return;
+  const double bias = q.bias ? (double)q.bias[j] : 0.0;
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int i = i0 + 2 * ty + a, j = j0 + 2 * tx + b;
-      if (i >= q.rows || j >= q.cols) continue;
-      const double v = acc[a][b] + (q.bias ? (double)q.bias[j] : 0.0);
-      const int64_t o = (int64_t)i * q.ld + j;
-      if (q.out_dbl)
-        static_cast<double*>(q.out)[o] = v;
-      else
-        static_cast<float*>(q.out)[o] = (float)v;
-    }
+  for (int e = 0; e < 4; ++e) {  // (the fp64 MFMA's output row 4 e + g)
+    const int i = i0 + 4 * e + g;
+    if (i >= q.rows) continue;
+    const double v = acc[e] + bias;
+    const int64_t o = (int64_t)i * q.ld + j;
+    if (q.out_type == kOutF64)
+      static_cast<double*>(q.out)[o] = v;
+    else if (q.out_type == kOutBF16)
+      static_cast<bf16*>(q.out)[o] = (bf16)(float)v;
+    else
+      static_cast<float*>(q.out)[o] = (float)v;
+  }
 }
 
 // The product of a batch is chosen with constant indices (a run-time index
@@ -121,138 +116,93 @@ __global__ void __launch_bounds__(kMMThreads) k_mm64(MM64Batch b) {
     case I:             \
       if (I < b.n) mm64_tile(b.p[I]); \
       break;
-    PA_MM64_CASE(0) PA_MM64_CASE(1) PA_MM64_CASE(2)
+    PA_MM64_CASE(0) PA_MM64_CASE(1) PA_MM64_CASE(2) PA_MM64_CASE(3)
+    PA_MM64_CASE(4) PA_MM64_CASE(5) PA_MM64_CASE(6)
 #undef PA_MM64_CASE
     default:
       break;
   }
 }
 
-constexpr int kCoreThreads = 256;
-
-// Lanes per softmax row: 256 / (M rounded up to a power of two), at most a
-// wave, so a row's lanes stay inside one wave.
-__device__ __forceinline__ int core_row_lanes(int M) {
-  int mp = 1;
-  while (mp < M) mp <<= 1;
-  const int g = kCoreThreads / mp;
-  return g < 64 ? g : 64;
-}
-
-template <typename Op>
-__device__ __forceinline__ double lanes_reduce64(double v, int G, Op op) {
-  for (int o = 1; o < G; o <<= 1) v = op(v, __shfl_xor(v, o));
-  return v;
-}
-
-// Head matrices [M][D] of head h: staged in LDS rows of stride D + 1 when
-// they fit (STAGE), else read from global memory.
-struct HeadMat {
-  const double* g;  // global [M][C] at the head's columns
-  double* s;        // LDS [M][D + 1]
-  int C, DS;
-};
-template <bool STAGE>
-__device__ __forceinline__ double at(const HeadMat& m, int r, int d) {
-  return STAGE ? m.s[r * m.DS + d] : m.g[(int64_t)r * m.C + d];
-}
-template <bool STAGE, typename TS>
-__device__ __forceinline__ void stage_mat(HeadMat& m, const TS* src, int M, int D, int C,
-                                          int off, double* lds) {
-  m.g = nullptr;
-  m.s = lds;
-  m.C = C;
-  m.DS = D + 1;
-  for (int e = threadIdx.x; e < M * D; e += kCoreThreads) {
-    const int r = e / D, d = e - r * D;
-    lds[r * (D + 1) + d] = (double)src[(int64_t)r * C + off + d];
-  }
-}
-
-// P = softmax(Q_h K_h^T * scale) into ps ([M][M + 1], LDS): scores from the
-// staged heads, then G lanes per row (max, exponentials, sum, normalise).
-template <bool STAGE>
-__device__ __forceinline__ void core64_probs(const HeadMat& q, const HeadMat& k, int M, int D,
-                                             double* ps) {
-  const int MS = M + 1;
-  const double scale = 1.0 / sqrt((double)D);
-  for (int e = threadIdx.x; e < M * M; e += kCoreThreads) {
-    const int r = e / M, c = e - r * M;
-    double s = 0.0;
-    for (int d = 0; d < D; ++d) s = fma(at<STAGE>(q, r, d), at<STAGE>(k, c, d), s);
-    ps[r * MS + c] = s * scale;
-  }
-  __syncthreads();
-  const int G = core_row_lanes(M), r = threadIdx.x / G, li = threadIdx.x - r * G;
-  double mx = -INFINITY;
-  if (r < M)
-    for (int c = li; c < M; c += G) mx = fmax(mx, ps[r * MS + c]);
-  mx = lanes_reduce64(mx, G, [](double a, double b) { return fmax(a, b); });
-  double sum = 0.0;
-  if (r < M)
-    for (int c = li; c < M; c += G) {
-      const double e = exp(ps[r * MS + c] - mx);
-      ps[r * MS + c] = e;
-      sum += e;
-    }
-  sum = lanes_reduce64(sum, G, [](double a, double b) { return a + b; });
-  const double inv = 1.0 / sum;
-  if (r < M)
-    for (int c = li; c < M; c += G) ps[r * MS + c] *= inv;
-  __syncthreads();
-}
-
-// O_h = P V_h into global O (rows at stride C, the head's columns).
-template <bool STAGE, typename TO>
-__device__ __forceinline__ void core64_pv(const double* ps, const HeadMat& v, int M, int D, int C,
-                                          int off, TO* O) {
-  const int MS = M + 1;
-  for (int e = threadIdx.x; e < M * D; e += kCoreThreads) {
-    const int r = e / D, d = e - r * D;
-    double s = 0.0;
-    for (int c = 0; c < M; ++c) s = fma(ps[r * MS + c], at<STAGE>(v, c, d), s);
-    O[(int64_t)r * C + off + d] = (TO)s;
-  }
-}
-
-template <bool STAGE>
-__device__ __forceinline__ HeadMat head_mat(const double* g, int M, int D, int C, int off,
-                                            double*& lds) {
-  HeadMat m;
-  if (STAGE) {
-    stage_mat<true>(m, g, M, D, C, off, lds);
-    lds += M * (D + 1);
-  } else {
-    m.g = g + off;
-    m.s = nullptr;
-    m.C = C;
-    m.DS = D + 1;
-  }
-  return m;
-}
-
-template <bool STAGE, typename TO>
-__global__ void __launch_bounds__(kCoreThreads) k_core64(const double* Q, const double* K,
-                                                         const double* V, TO* O, int M, int C,
-                                                         int H) {
-  extern __shared__ __attribute__((aligned(16))) double dsm[];
+// Head blockIdx.x, query rows 16 blockIdx.y ..: the scores are formed
+// transposed (K_h Q_h^T), so that lane (r, g) holds query r's scores of the
+// keys 16 t + 4 e + g: the softmax reduces in the lane and over the four lane
+// groups, and the probabilities are already the B operand of O_h^T = V_h^T
+// P^T (step (t, e): key 16 t + 4 e + g).
+template <int MT, typename TO>
+__global__ void __launch_bounds__(64) k_core64(const double* Q, const double* K, const double* V,
+                                               TO* O, int M, int C, int H) {
   const int D = C / H, off = blockIdx.x * D;
-  double* ps = dsm;  // [M][M+1]
-  double* lds = dsm + M * (M + 1);
-  const HeadMat q = head_mat<STAGE>(Q, M, D, C, off, lds);
-  const HeadMat k = head_mat<STAGE>(K, M, D, C, off, lds);
-  const HeadMat v = head_mat<STAGE>(V, M, D, C, off, lds);
-  if (STAGE) __syncthreads();
-  core64_probs<STAGE>(q, k, M, D, ps);
-  core64_pv<STAGE>(ps, v, M, D, C, off, O);
+  const int lane = lane_id(), r = lane & 15, g = lane >> 4;
+  const int qi = 16 * blockIdx.y + r;
+  const double* qp = Q + (int64_t)(qi < M ? qi : M - 1) * C + off;
+  const double* kp[MT];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    const int j = 16 * t + r;
+    kp[t] = K + (int64_t)(j < M ? j : M - 1) * C + off;
+  }
+  f64x4 p[MT];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) p[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int d0 = 0; d0 < D; d0 += 4) {
+    const int d = d0 + g;
+    const bool in = d < D;
+    const double qv = in ? qp[in ? d : 0] : 0.0;
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      const double kv = in ? kp[t][in ? d : 0] : 0.0;
+      p[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(kv, qv, p[t], 0, 0, 0);
+    }
+  }
+  const double scale = 1.0 / sqrt((double)D);
+  double mx = -INFINITY;
+#pragma unroll
+  for (int t = 0; t < MT; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      p[t][e] = 16 * t + 4 * e + g < M ? p[t][e] * scale : -INFINITY;
+      mx = fmax(mx, p[t][e]);
+    }
+  mx = fmax(mx, __shfl_xor(mx, 16));
+  mx = fmax(mx, __shfl_xor(mx, 32));
+  double sum = 0.0;
+#pragma unroll
+  for (int t = 0; t < MT; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      p[t][e] = exp(p[t][e] - mx);
+      sum += p[t][e];
+    }
+  sum += __shfl_xor(sum, 16);
+  sum += __shfl_xor(sum, 32);
+  const double inv = 1.0 / sum;
+#pragma unroll
+  for (int t = 0; t < MT; ++t) p[t] *= inv;
+  for (int d0 = 0; d0 < D; d0 += 16) {
+    const int d = d0 + r < D ? d0 + r : D - 1;  // (rows d >= D are not stored)
+    f64x4 o{0.0, 0.0, 0.0, 0.0};
+    double v[MT][4];
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int j = 16 * t + 4 * e + g;
+        v[t][e] = V[(int64_t)(j < M ? j : M - 1) * C + off + d];
+      }
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int j = 16 * t + 4 * e + g;
+        o = __builtin_amdgcn_mfma_f64_16x16x4f64(j < M ? v[t][e] : 0.0, p[t][e], o, 0, 0, 0);
+      }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (d0 + 4 * e + g < D && qi < M) O[(int64_t)qi * C + off + d0 + 4 * e + g] = (TO)o[e];
+  }
 }
-
-// LDS of the core kernel: P, plus the staged head matrices.
-size_t core64_lds(int M, int D, bool stage) {
-  const size_t hm = stage ? (size_t)3 * M * (D + 1) : 0;
-  return ((size_t)M * (M + 1) + hm) * sizeof(double);
-}
-constexpr size_t kCoreLdsMax = 150 * 1024;
 
 bool core64_ok(int M, int C, int H) { return M >= 1 && M <= 64 && H >= 1 && C % H == 0; }
 
@@ -263,7 +213,7 @@ hipError_t launch_mm64(const MM64Batch& b, hipStream_t st) {
   int tiles = 0;
   for (int i = 0; i < b.n; ++i) {
     const MM64& q = b.p[i];
-    if (q.rows < 1 || q.cols < 1 || q.nt < 1 || q.nt > 3 || !q.out || q.ld < q.cols)
+    if (q.rows < 1 || q.cols < 1 || q.nt < 0 || q.nt > 3 || !q.out || q.ld < q.cols)
       return hipErrorInvalidValue;
     for (int t = 0; t < q.nt; ++t)
       if (q.K[t] < 1) return hipErrorInvalidValue;
@@ -277,16 +227,20 @@ hipError_t launch_mm64(const MM64Batch& b, hipStream_t st) {
 hipError_t launch_core64(const double* Q, const double* K, const double* V, void* O, bool O_dbl,
                          int M, int C, int H, hipStream_t st) {
   if (!Q || !K || !V || !O || !core64_ok(M, C, H)) return hipErrorInvalidValue;
-  const int D = C / H;
-  const bool stage = core64_lds(M, D, true) <= kCoreLdsMax;
-  const size_t lds = core64_lds(M, D, stage);
-#define PA_CORE64(S, TO) \
-  hipLaunchKernelGGL((k_core64<S, TO>), dim3(H), dim3(kCoreThreads), lds, st, Q, K, V, \
+  const int MT = (M + 15) / 16;
+#define PA_CORE64(T, TO)                                                               \
+  hipLaunchKernelGGL((k_core64<T, TO>), dim3(H, MT), dim3(64), 0, st, Q, K, V,         \
                      static_cast<TO*>(O), M, C, H)
-  if (stage) {
-    if (O_dbl) PA_CORE64(true, double); else PA_CORE64(true, float);
-  } else {
-    if (O_dbl) PA_CORE64(false, double); else PA_CORE64(false, float);
+  switch (MT * 2 + (O_dbl ? 1 : 0)) {
+    case 2: PA_CORE64(1, float); break;
+    case 3: PA_CORE64(1, double); break;
+    case 4: PA_CORE64(2, float); break;
+    case 5: PA_CORE64(2, double); break;
+    case 6: PA_CORE64(3, float); break;
+    case 7: PA_CORE64(3, double); break;
+    case 8: PA_CORE64(4, float); break;
+    case 9: PA_CORE64(4, double); break;
+    default: return hipErrorInvalidValue;
   }
 #undef PA_CORE64
   return hipGetLastError();
