@@ -218,7 +218,7 @@ pa_status pa_slice_aggregate_w(const pa_dims* dims, const void* x, const void* G
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * computation as pa_slice_aggregate, bit for bit, with no workspace
- * argument.  Its table image and per-block partial records live in a
+ * argument.  Its per-block partial records live in a
  * static device array of the library (17 MiB on each device it runs on,
  * held until the process ends); the call allocates and frees nothing.
  * Shapes whose scratch would exceed the array return PA_ERR_UNSUPPORTED

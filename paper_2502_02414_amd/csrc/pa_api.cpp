@@ -60,12 +60,6 @@ struct Layout {
 
 Layout layout_of(const pa_dims& d) {
   Layout L{};
-  const int MB = mblocks(d.M);
-  size_t img = 0;
-  for (int pass = 0; pass < pa::kNumPasses; ++pass) {
-    size_t b = pa::image_bytes(pass, d.dtype, cpad(d.C), MB);
-    if (b > img) img = b;
-  }
   // chunks: every pass uses at most kPartialsMax blocks
   const int64_t rec = (int64_t)d.C * d.M + d.M + d.C + 1;  // the largest record
   const int P = pa::kPartialsMax;
@@ -74,7 +68,7 @@ Layout layout_of(const pa_dims& d) {
   // and the attention matrices of the heads
   const size_t attn = (16 * mc + (size_t)d.H * d.M * d.M) * sizeof(float);
   L.img = 0;
-  L.parts = up(img);
+  L.parts = up(pa::image_bytes(d.dtype, cpad(d.C), mblocks(d.M)));
   L.attn = L.parts + up((size_t)P * rec * sizeof(float));
   L.total = L.attn + up(attn);
   L.P = P;
@@ -145,7 +139,7 @@ pa::PrepArgs prep_of(const pa_dims& d, int pass, const pa_slice_params* sp, void
   p.M = d.M;
   p.MB = mblocks(d.M);
   p.eps = d.eps;
-  if (sp) {  // (the stored-weights deslice builds no logits table)
+  if (sp) {
     p.A = sp->A;
     p.b = sp->b;
     p.a = sp->a;
@@ -161,6 +155,11 @@ pa::StreamLaunch stream_of(const pa_dims& d, int pass, const void* x, const void
   L.x = x;
   L.G = G;
   L.img = wsb(ws) + lay.img;
+  if (sp) {  // (the stored-weights passes have no logits table)
+    L.tab.A = sp->A;
+    L.tab.b = sp->b;
+    L.tab.a = sp->a;
+  }
   L.partials = reinterpret_cast<float*>(wsb(ws) + lay.parts);
   L.N = d.N;
   L.M = d.M;
@@ -305,7 +304,6 @@ pa_status pa_slice_weights(const pa_dims* dims, const void* x, const void* G,
   PA_TRY(check_pass(*dims, pa::kWeights));
   PA_TRY(check_ws(*dims, ws, ws_bytes));
   hipStream_t st = as_stream(stream);
-  PA_HIP(pa::launch_prep(prep_of(*dims, pa::kWeights, sp, ws), st), "prep");
   pa::StreamLaunch L = stream_of(*dims, pa::kWeights, x, G, sp, ws);
   L.out = W;
   L.tau_out = tau;
@@ -329,11 +327,10 @@ pa_status check_aggregate(int pass, const pa_dims* dims, const void* x, const vo
 }
 
 // The launches of pa_slice_aggregate(_w) on a validated workspace: the
-// table image at its start, the block records at the layout's offset.
+// block records at the layout's offset.
 pa_status slice_aggregate_launch(int pass, const pa_dims* dims, const void* x, const void* G,
                                  const pa_slice_params* sp, float* num, float* den, float* S,
                                  void* W, void* ws, hipStream_t st) {
-  PA_HIP(pa::launch_prep(prep_of(*dims, pass, sp, ws), st), "prep");
   pa::StreamLaunch L = stream_of(*dims, pass, x, G, sp, ws);
   L.out = W;
   PA_HIP(run_stream(pass, *dims, L, st), "slice aggregate");
@@ -378,9 +375,8 @@ pa_status pa_slice_aggregate_w(const pa_dims* dims, const void* x, const void* G
 }  // extern "C"
 
 // ---------------------------------------------------------------------------
-// pa_slice_aggregate_noalloc: the aggregate's table image and block records
-// in a static device array instead of a caller's workspace.  Each device
-// holds its own copy of the array for the life of the process; host code
+// pa_slice_aggregate_noalloc: the aggregate's block records in a static
+// device array instead of a caller's workspace.  Each device holds its own copy of the array for the life of the process; host code
 // uses only the address hipGetSymbolAddress returns for it on that device
 // (the array's name is a host-side stand-in, not a device address).
 // ---------------------------------------------------------------------------
@@ -416,7 +412,7 @@ pa_status noalloc_scratch(void** out) {
 }
 
 // Scratch bytes the aggregate needs: the workspace layout up to the end of
-// the aggregate's own block records (its table image sits at offset 0).
+// the aggregate's own block records.
 size_t noalloc_bytes(const pa_dims& d) {
   return layout_of(d).parts +
          (size_t)chunks(d, pa::kAggregate) * pa::record_floats(pa::kAggregate, d.C, d.M) *
@@ -451,10 +447,8 @@ pa_status pa_deslice_w(const pa_dims* dims, const void* W, const float* Sp, void
   PA_TRY(check_pass(*dims, pa::kDesliceW));
   PA_TRY(check_ws(*dims, ws, ws_bytes));
   hipStream_t st = as_stream(stream);
-  pa::PrepArgs p = prep_of(*dims, pa::kDesliceW, nullptr, ws);
-  p.Sp = Sp;
-  PA_HIP(pa::launch_prep(p, st), "prep");
   pa::StreamLaunch L = stream_of(*dims, pa::kDesliceW, nullptr, W, nullptr, ws);
+  L.tab.Sp = Sp;
   L.out = y;
   PA_HIP(run_stream(pa::kDesliceW, *dims, L, st), "deslice (stored weights)");
   return PA_OK;
@@ -694,10 +688,8 @@ pa_status pa_deslice(const pa_dims* dims, const void* x, const void* G,
   PA_TRY(check_pass(*dims, pa::kDeslice));
   PA_TRY(check_ws(*dims, ws, ws_bytes));
   hipStream_t st = as_stream(stream);
-  pa::PrepArgs p = prep_of(*dims, pa::kDeslice, sp, ws);
-  p.Sp = Sp;
-  PA_HIP(pa::launch_prep(p, st), "prep");
   pa::StreamLaunch L = stream_of(*dims, pa::kDeslice, x, G, sp, ws);
+  L.tab.Sp = Sp;
   L.out = y;
   PA_HIP(run_stream(pa::kDeslice, *dims, L, st),
          "deslice");
@@ -713,7 +705,6 @@ pa_status pa_deslice_backward(const pa_dims* dims, const void* x, const void* G,
   PA_TRY(check_pass(*dims, pa::kDesliceBwd));
   PA_TRY(check_ws(*dims, ws, ws_bytes));
   hipStream_t st = as_stream(stream);
-  PA_HIP(pa::launch_prep(prep_of(*dims, pa::kDesliceBwd, sp, ws), st), "prep");
   pa::StreamLaunch L = stream_of(*dims, pa::kDesliceBwd, x, G, sp, ws);
   L.dY = dY;
   PA_HIP(run_stream(pa::kDesliceBwd, *dims, L, st),
@@ -775,7 +766,7 @@ pa_status pa_slice_aggregate_backward(const pa_dims* dims, const void* x, const 
   p.den = den;
   p.dS = dS;
   p.Sp = Sp;
-  PA_HIP(pa::launch_prep(p, st), "prep");
+  PA_HIP(pa::launch_prep_back(p, st), "prep");
   pa::StreamLaunch L = stream_of(*dims, pa::kSliceBwd, x, G, sp, ws);
   L.dY = dY;
   L.out = dx;
@@ -857,6 +848,11 @@ pa::StreamLaunch heads_stream(const pa_dims& d, int pass, const void* x, const v
   L.hs_x = L.hs_dy = L.hs_out = hc.sx;
   L.hs_g = hc.sg;
   L.hs_img = L.hs_part = hc.wtot;
+  L.tab.A = hp->A;
+  L.tab.b = hp->b;
+  L.tab.a = hp->a;
+  L.hs_A = hc.sA; L.hs_b = hc.sb; L.hs_a = hc.sa;
+  L.hs_Sp = hc.sMD;
   // tau0 + b_t in double, b_t the head's device scalar (as b_t_dev adds it)
   L.tb = (double)d.tau0;
   L.tb_dev = hp->b_t;
@@ -893,7 +889,6 @@ pa_status pa_heads_slice_aggregate(const pa_dims* dims, int heads, const void* x
   PA_TRY(check_heads_ws(*dims, heads, ws, ws_bytes));
   hipStream_t st = as_stream(stream);
   const pa_dims& d = *dims;
-  PA_HIP(pa::launch_prep(heads_prep(d, pa::kAggregate, hp, hc, ws), st), "prep");
   pa::StreamLaunch L = heads_stream(d, pa::kAggregate, x, G, hp, hc, ws);
   PA_HIP(run_stream(pa::kAggregate, d, L, st), "per-head slice aggregate");
   pa::Segments seg = heads_segments(hc);
@@ -920,10 +915,8 @@ pa_status pa_heads_deslice(const pa_dims* dims, int heads, const void* x, const 
   PA_TRY(check_heads_ws(*dims, heads, ws, ws_bytes));
   hipStream_t st = as_stream(stream);
   const pa_dims& d = *dims;
-  pa::PrepArgs p = heads_prep(d, pa::kDeslice, hp, hc, ws);
-  p.Sp = Sp;
-  PA_HIP(pa::launch_prep(p, st), "prep");
   pa::StreamLaunch L = heads_stream(d, pa::kDeslice, x, G, hp, hc, ws);
+  L.tab.Sp = Sp;
   L.out = y;
   PA_HIP(run_stream(pa::kDeslice, d, L, st), "per-head deslice");
   return PA_OK;
@@ -940,7 +933,6 @@ pa_status pa_heads_deslice_backward(const pa_dims* dims, int heads, const void* 
   PA_TRY(check_heads_ws(*dims, heads, ws, ws_bytes));
   hipStream_t st = as_stream(stream);
   const pa_dims& d = *dims;
-  PA_HIP(pa::launch_prep(heads_prep(d, pa::kDesliceBwd, hp, hc, ws), st), "prep");
   pa::StreamLaunch L = heads_stream(d, pa::kDesliceBwd, x, G, hp, hc, ws);
   L.dY = dY;
   PA_HIP(run_stream(pa::kDesliceBwd, d, L, st), "per-head deslice backward");
@@ -979,7 +971,7 @@ pa_status pa_heads_slice_aggregate_backward(const pa_dims* dims, int heads, cons
   p.den = den;
   p.dS = dS;
   p.Sp = Sp;
-  PA_HIP(pa::launch_prep(p, st), "prep");
+  PA_HIP(pa::launch_prep_back(p, st), "prep");
   pa::StreamLaunch L = heads_stream(d, pa::kSliceBwd, x, G, hp, hc, ws);
   L.dY = dY;
   L.out = dx;
@@ -1010,7 +1002,7 @@ pa_status pa_slice_weights_backward(const pa_dims* dims, const void* x, const vo
   PA_TRY(check_pass(*dims, pa::kWeightsBwd));
   PA_TRY(check_ws(*dims, ws, ws_bytes));
   hipStream_t st = as_stream(stream);
-  PA_HIP(pa::launch_prep(prep_of(*dims, pa::kWeightsBwd, sp, ws), st), "prep");
+  PA_HIP(pa::launch_prep_back(prep_of(*dims, pa::kWeightsBwd, sp, ws), st), "prep");
   pa::StreamLaunch L = stream_of(*dims, pa::kWeightsBwd, x, G, sp, ws);
   L.dW = dW;
   L.dtau = dtau;

@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "pa_tables.hpp"
+
 namespace pa {
 
 // Heads of one batched per-head call (pa_heads_*): head h = blockIdx.y of
@@ -16,7 +18,8 @@ struct StreamLaunch {
   const void* x = nullptr;
   const void* G = nullptr;
   const void* dY = nullptr;
-  const void* img = nullptr;
+  TableSrc tab{};             // the forward tables (pa_tables.hpp)
+  const void* img = nullptr;  // the backward passes' table image (k_prep_back)
   void* out = nullptr;
   float* tau_out = nullptr;
   const float* dW = nullptr;
@@ -33,9 +36,11 @@ struct StreamLaunch {
   bool states = false;
   bool deslice = false;
   // per-head batch: heads (gridDim.y), byte strides of x, G, dY, out, the
-  // table image, the partial records and tb_dev (each head's b_t)
+  // partial records, tb_dev (each head's b_t), the parameters (0: shared), S'
+  // and the table image
   int heads = 1;
-  int64_t hs_x = 0, hs_g = 0, hs_dy = 0, hs_out = 0, hs_img = 0, hs_part = 0, hs_tb = 0;
+  int64_t hs_x = 0, hs_g = 0, hs_dy = 0, hs_out = 0, hs_part = 0, hs_tb = 0;
+  int64_t hs_A = 0, hs_b = 0, hs_a = 0, hs_Sp = 0, hs_img = 0;
 };
 
 // Streaming passes (pass = pa::Pass).  dtype: 0 fp32, 1 bf16.
@@ -55,7 +60,8 @@ int probe_waves(int pass, int dtype, int C, int MB);
 hipError_t launch_probe(int pass, int dtype, int C, int MB, const StreamLaunch& L,
                         hipStream_t st);
 
-// Table image for a pass, written into `img` (device).
+// Table image of a backward pass (kSliceBwd, kWeightsBwd), written into `img`
+// (device).
 struct PrepArgs {
   int pass = 0;
   int dtype = 0;
@@ -65,7 +71,7 @@ struct PrepArgs {
   const void* A = nullptr;    // [cr,M] dtype
   const float* b = nullptr;   // [M]
   const void* a = nullptr;    // [cr] dtype
-  const float* Sp = nullptr;  // [M,cr]  (kDeslice, kSliceBwd deslice term)
+  const float* Sp = nullptr;  // [M,cr]  (kSliceBwd deslice term)
   const float* num = nullptr; // [M,cr]  (kSliceBwd states term)
   const float* den = nullptr; // [M]
   const float* dS = nullptr;  // [M,cr]
@@ -74,9 +80,9 @@ struct PrepArgs {
   int heads = 1;
   int64_t hs_A = 0, hs_b = 0, hs_a = 0, hs_Sp = 0, hs_num = 0, hs_den = 0, hs_dS = 0, hs_img = 0;
 };
-hipError_t launch_prep(const PrepArgs& p, hipStream_t st);
-// Bytes of the table image of a pass.
-size_t image_bytes(int pass, int dtype, int C, int MB);
+hipError_t launch_prep_back(const PrepArgs& p, hipStream_t st);
+// Bytes of that image.
+size_t image_bytes(int dtype, int C, int MB);
 
 // out[k] = sum_{p < P} partials[p * rec + k] (k < rec), in order p = 0..P-1,
 // scattered into up to 6 destination segments (each written to dst[i] and,

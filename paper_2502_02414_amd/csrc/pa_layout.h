@@ -1,6 +1,7 @@
 // Compile-time geometry shared by the host launchers and the gfx950 kernels:
-// the byte layout of the per-block LDS "table image" (built once per call by
-// the prep kernel into the workspace, then copied by every block into LDS),
+// the byte layout of the per-block LDS tables (the forward's built by every
+// block, the backward's once per call as an image in the workspace that every
+// block copies into LDS),
 // the per-wave LDS regions, and the partial-sum record sizes.
 #pragma once
 

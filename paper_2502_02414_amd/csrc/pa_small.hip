@@ -1,12 +1,9 @@
 // Small kernels around the streaming passes (gfx950):
-//   - the per-call table image (logits table [A^T ; a], deslice table S'^T,
-//     backward table [dnum | S'] with its centres, biases, dden) in the exact
-//     byte layout the streaming kernels copy into LDS (rows of the logits and
-//     backward tables padded as in pa_layout.h), one launch per call;
-//   - the ordered reduction of per-block partial-sum records (the partial
-//     sums of Section 4.2, here over point chunks of one GPU);
-//     with the states s_j = num_j / max(den_j, eps) (Eq. 1) formed there;
-// (token attention lives in pa_tokens.hip).
+//   - the table image of the backward passes, in the exact byte layout the
+//     streaming blocks copy into LDS (rows padded as in pa_layout.h);
+//   - the ordered reduction of the per-block partial-sum records (the partial
+//     sums of Section 4.2, here over point chunks of one GPU), with the states
+//     s_j = num_j / max(den_j, eps) (Eq. 1) formed there.
 #include <type_traits>
 
 #include "pa_device.hpp"
@@ -15,158 +12,150 @@
 
 namespace pa {
 
-// ---------------------------------------------------------------------------
-// Table image
-// ---------------------------------------------------------------------------
-struct PrepGeo {
-  int C, M, MB, M16, SZ;  // C: the tables' width (the parameters' cr <= C channels, zeros beyond)
-  int TROW, SROW, WROW, OFF_L, OFF_2;
-};
-
-static PrepGeo prep_geo(int dtype, int C, int M, int MB) {
-  PrepGeo g;
-  g.C = C; g.M = M; g.MB = MB; g.M16 = 16 * MB; g.SZ = dtype == 1 ? 2 : 4;
-  g.TROW = C * g.SZ + 32;
-  g.SROW = g.M16 * g.SZ + 16;
-  g.WROW = 2 * C * g.SZ + 32;
-  g.OFF_L = (3 * g.M16 + 3 * C) * 4;  // header: bias, dden, cN, cS, sw, a
-  g.OFF_2 = g.OFF_L + (g.M16 + 1) * g.TROW;
-  return g;
-}
-
-size_t image_bytes(int pass, int dtype, int C, int MB) {
-  PrepGeo g = prep_geo(dtype, C, 16 * MB, MB);
-  if (pass == kDeslice || pass == kDesliceW) return (size_t)g.OFF_2 + (size_t)C * g.SROW;
-  if (pass == kDesliceBwdW) return 0;
-  if (pass == kSliceBwd || pass == kWeightsBwd) return (size_t)g.OFF_2 + (size_t)g.M16 * g.WROW;
-  return (size_t)g.OFF_2;
-}
-
-// The backward header and table (kSliceBwd, kWeightsBwd), block `bid` of
-// M + ceil(2C/256):
-//   blocks [0, M): dden_j (chain rule of Eq. 1; 0 when den_j < eps), reduced
-//     over C in a fixed tree, and sw_j = w_j / sum w;
-//   the others: one column cc of the backward table per thread (dnum for
-//     cc < C, s' beyond), its centre cN[c] / cS[c] and its M16 rows.
-// Any centre common to all slices leaves the softmax backward unchanged;
-// the mean weighted by w_j = max(den_j, 0) (the slices' share of the points)
-// keeps a slice with a tiny or floored denominator -- whose dnum_j =
-// dS_j / max(den_j, eps) can be huge -- from dragging the centre away from
-// the rows that carry weight, and keeps the small differences between nearly
-// equal rows out of the rounding.  Without the states term den is not given
-// and the weights are uniform; kWeightsBwd has neither term (zeros).
-template <typename T>
-__device__ __forceinline__ void prep_back(const PrepGeo& g, const PrepArgs& p, int bid,
-                                          float* red) {
-  char* img = reinterpret_cast<char*>(p.img);
-  float* hdr = reinterpret_cast<float*>(img);
-  const int C = g.C, M = g.M, M16 = g.M16, cr = p.cr;
-  const bool states = p.dS != nullptr && p.pass == kSliceBwd;
-  const bool desl = p.Sp != nullptr && p.pass == kSliceBwd;
-  if (bid < M) {
-    const int j = bid;
-    // loads first: den_j, row j of dS and num (one element per thread for
-    // C <= 256), and in wave 0 the weights w_k (one slice per lane)
-    const float dj = states ? p.den[j] : 1.f;
-    float s = 0.f;
-    for (int c = threadIdx.x; c < cr; c += 256) {
-      const float dv = states ? p.dS[j * cr + c] : 0.f, nv = states ? p.num[j * cr + c] : 0.f;
-      s += dv * (nv / dj);
-    }
-    const int k = threadIdx.x < 64 ? (int)threadIdx.x : 0;
-    const float wk = k < M ? (states ? fmaxf(p.den[k < M ? k : 0], 0.f) : 1.f) : 0.f;
-    const bool live = states && dj >= p.eps;
-    red[threadIdx.x] = live ? s : 0.f;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-      if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-      __syncthreads();
-    }
-    float wsum = wk;  // wave 0: fixed-order butterfly over the slices
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) wsum += __shfl_xor(wsum, o);
-    if (threadIdx.x == 0) {
-      hdr[M16 + j] = live ? -red[0] / dj : 0.f;
-      hdr[2 * M16 + 2 * C + j] = (states ? fmaxf(dj, 0.f) : 1.f) / wsum;
-    }
-    if (j == 0)
-      for (int q = M + threadIdx.x; q < M16; q += blockDim.x) {
-        hdr[M16 + q] = 0.f;
-        hdr[2 * M16 + 2 * C + q] = 0.f;
-      }
-    return;
-  }
-  // per slice (once per block, in LDS): the weight w_j and 1 / max(den_j, eps)
-  float* wl = red;
-  float* rl = red + 64;
-  if (threadIdx.x < 64) {
-    const int j = threadIdx.x < M ? (int)threadIdx.x : M - 1;
-    const float dj = states ? p.den[j] : 1.f;
-    wl[threadIdx.x] = states ? fmaxf(dj, 0.f) : 1.f;
-    rl[threadIdx.x] = 1.0f / (dj >= p.eps ? dj : p.eps);
-  }
-  __syncthreads();
-  const int cc = (bid - M) * blockDim.x + threadIdx.x;
-  if (cc >= 2 * C) return;
-  const bool first = cc < C;
-  const int c = first ? cc : cc - C;
-  // (columns c >= cr are padding: zero rows, centre 0)
-  const bool on = (first ? states : desl) && c < cr;
-  const int cl = c < cr ? c : 0;
-  // the column's values, all loads issued at once (M <= 64)
-  float v[64];
-#pragma unroll
-  for (int j = 0; j < 64; ++j) {
-    const int jj = j < M ? j : M - 1;
-    v[j] = on ? (first ? p.dS[jj * cr + cl] : p.Sp[jj * cr + cl]) : 0.f;
-  }
-  float wsum = 0.f, sum = 0.f;
-#pragma unroll
-  for (int j = 0; j < 64; ++j) {
-    if (j < M) {
-      if (first) v[j] *= rl[j];  // dnum_j
-      wsum += wl[j];
-      sum += wl[j] * v[j];
-    }
-  }
-  const float ctr = on && wsum > 0.f ? sum * (1.0f / wsum) : 0.f;
-  hdr[2 * M16 + cc] = ctr;  // cN[c] (cc < C), then cS[c]
-#pragma unroll
-  for (int j = 0; j < 64; ++j)
-    if (j < M16)
-      *reinterpret_cast<T*>(img + g.OFF_2 + lds_off(j, cc * g.SZ, g.WROW)) =
-          from_f<T>(on && j < M ? v[j] - ctr : 0.f);
-}
-
-// The table image of a pass: for the backward passes the blocks
-// [0, M + ceil(2C/256)) build the backward header and table (prep_back),
-// the rest (grid-stride) the bias and a header, the logits table [A^T ; a]
-// and, for kDeslice, S'^T.
-// The deslice table S'^T (row c, column j; columns j >= M zero) at OFF_2.
-template <typename T>
-__device__ __forceinline__ void prep_deslice_table(const PrepGeo& g, const PrepArgs& p, char* img,
-                                                   int64_t tid, int64_t nth) {
-  const int C = g.C, M = g.M, M16 = g.M16, cr = p.cr;
-  const int64_t nS = (int64_t)C * M16;
-#pragma unroll 4
-  for (int64_t k = tid; k < nS; k += nth) {
-    const int c = (int)(k / M16), j = (int)(k - (int64_t)c * M16);
-    const float v = (j < M && c < cr) ? p.Sp[j * cr + c] : 0.f;
-    *reinterpret_cast<T*>(img + g.OFF_2 + c * g.SROW + j * g.SZ) = from_f<T>(v);
-  }
-}
-
-// A per-head batch builds head blockIdx.y's image from its parameters and
-// states at the batch's byte strides (a stride of 0: shared by the heads).
+// A per-head batch: head blockIdx.y's tensor at the batch's byte stride.
 template <typename Q>
 __device__ __forceinline__ Q* head_at(Q* q, int64_t stride) {
   using B = typename std::conditional<std::is_const<Q>::value, const char*, char*>::type;
   return q ? reinterpret_cast<Q*>(reinterpret_cast<B>(q) + (int64_t)blockIdx.y * stride) : q;
 }
 
+// ---------------------------------------------------------------------------
+// The backward passes' table image: header (biases, dden, centres, shares, a),
+// logits table [A^T ; a] and the centred table [dnum - cN | s' - cS].
+//
+// Bound by latency: a few hundred kilobytes, so every block has one round of
+// loads, one reduction and its stores, and the work is spread over M16 + 1 +
+// 2C/64 blocks (the form before had two dependent rounds and all of the table
+// in 2C/256 blocks: 10 to 12 us per call).
+//
+// Blocks [0, M16]: row j of the logits table (j = M16: a, and the header's
+//   biases, shares and fp32 a), and dden_j (chain rule of Eq. 1; 0 when den_j
+//   < eps), reduced over C in a fixed tree.
+// The others: 64 columns cc of the backward table (dnum for cc < C, s' beyond),
+//   a quarter of the slices per wave, and their centres cN[c], cS[c].
+// Any centre common to all slices leaves the softmax backward unchanged; the
+// mean weighted by w_j = max(den_j, 0) (the slices' share of the points) keeps
+// a slice with a tiny or floored denominator -- whose dnum_j = dS_j /
+// max(den_j, eps) can be huge -- from dragging the centre away from the rows
+// that carry weight, and keeps the small differences between nearly equal
+// rows out of the rounding.  Without the states term den is not given and the
+// weights are uniform; kWeightsBwd has neither term (zeros).
+// ---------------------------------------------------------------------------
+struct PrepGeo {
+  int C, M, M16, SZ;  // C: the tables' width (the parameters' cr <= C channels, zeros beyond)
+  int TROW, WROW, OFF_L, OFF_2;
+};
+
+static PrepGeo prep_geo(int dtype, int C, int M, int MB) {
+  PrepGeo g;
+  g.C = C; g.M = M; g.M16 = 16 * MB; g.SZ = dtype == 1 ? 2 : 4;
+  g.TROW = C * g.SZ + 32;
+  g.WROW = 2 * C * g.SZ + 32;
+  g.OFF_L = (3 * g.M16 + 3 * C) * 4;  // header: bias, dden, cN, cS, sw, a
+  g.OFF_2 = g.OFF_L + (g.M16 + 1) * g.TROW;
+  return g;
+}
+
+size_t image_bytes(int dtype, int C, int MB) {
+  const PrepGeo g = prep_geo(dtype, C, 16 * MB, MB);
+  return (size_t)g.OFF_2 + (size_t)g.M16 * g.WROW;
+}
+
+// Row j of the logits table, dden_j, and (j = M16) the rest of the header;
+// thread t: channel t (C <= 256).
 template <typename T>
-__global__ void __launch_bounds__(256) k_prep(PrepGeo g, PrepArgs p) {
-  __shared__ float red[256];
+__device__ __forceinline__ void prep_row(const PrepGeo& g, const PrepArgs& p, int j, float* red) {
+  char* img = reinterpret_cast<char*>(p.img);
+  float* hdr = reinterpret_cast<float*>(img);
+  const T* A = reinterpret_cast<const T*>(p.A);
+  const T* av = reinterpret_cast<const T*>(p.a);
+  const int C = g.C, M = g.M, M16 = g.M16, cr = p.cr, t = threadIdx.x;
+  const bool states = p.dS != nullptr && p.pass == kSliceBwd;
+  const bool row = j < M16;
+  T v = from_f<T>(0.f);
+  if (t < cr) {
+    if (row && j < M) v = A[(int64_t)t * M + j];
+    if (!row && av) v = av[t];
+  }
+  if (t < C) {
+    *reinterpret_cast<T*>(img + g.OFF_L + lds_off(j, t * g.SZ, g.TROW)) = v;
+    if (!row) hdr[3 * M16 + 2 * C + t] = to_f<T>(v);
+  }
+  if (row) {
+    const bool on = states && j < M;
+    const float dj = on ? p.den[j] : 1.f;
+    float s = on && t < cr ? p.dS[j * cr + t] * (p.num[j * cr + t] / dj) : 0.f;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) s += __shfl_xor(s, o);
+    if ((t & 63) == 0) red[t >> 6] = s;
+    __syncthreads();
+    if (t == 0) {
+      const float sum = (red[0] + red[1]) + (red[2] + red[3]);
+      hdr[M16 + j] = on && dj >= p.eps ? -sum / dj : 0.f;
+      // padded slices j >= M get bias -inf: their softmax weight is exactly 0
+      hdr[j] = j < M ? (p.b ? p.b[j] : 0.f) : -INFINITY;
+    }
+  } else if (t < 64) {
+    const float wk = t < M ? (states ? fmaxf(p.den[t], 0.f) : 1.f) : 0.f;
+    float wsum = wk;  // fixed-order butterfly over the slices
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) wsum += __shfl_xor(wsum, o);
+    if (t < M16) hdr[2 * M16 + 2 * C + t] = wk / wsum;
+  }
+}
+
+// 64 columns of the backward table: lane l column 64 bid + l, wave w the
+// slices [w M16 / 4, (w + 1) M16 / 4).
+template <typename T>
+__device__ __forceinline__ void prep_columns(const PrepGeo& g, const PrepArgs& p, int bid,
+                                             float* red) {
+  char* img = reinterpret_cast<char*>(p.img);
+  float* hdr = reinterpret_cast<float*>(img);
+  const int C = g.C, M = g.M, M16 = g.M16, cr = p.cr;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, per = M16 / 4, j0 = wave * per;
+  const bool states = p.dS != nullptr && p.pass == kSliceBwd;
+  const bool desl = p.Sp != nullptr && p.pass == kSliceBwd;
+  const int cc = 64 * bid + lane;  // (2C is a multiple of 64)
+  const bool first = cc < C;
+  const int c = first ? cc : cc - C;
+  // (columns c >= cr are padding: zero rows, centre 0)
+  const bool on = (first ? states : desl) && c < cr;
+  const float* src = first ? p.dS : p.Sp;
+  float v[16], d[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const bool in = k < per && j0 + k < M;
+    const int j = in ? j0 + k : 0;
+    v[k] = on && in ? src[j * cr + c] : 0.f;
+    d[k] = states && in ? p.den[j] : 1.f;
+  }
+  float wsum = 0.f, sum = 0.f;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    if (k < per && j0 + k < M) {
+      const float w = states ? fmaxf(d[k], 0.f) : 1.f;
+      if (first) v[k] *= 1.0f / (d[k] >= p.eps ? d[k] : p.eps);  // dnum_j
+      wsum += w;
+      sum += w * v[k];
+    }
+  }
+  red[64 * wave + lane] = sum;
+  red[256 + 64 * wave + lane] = wsum;
+  __syncthreads();
+  sum = (red[lane] + red[64 + lane]) + (red[128 + lane] + red[192 + lane]);
+  wsum = (red[256 + lane] + red[320 + lane]) + (red[384 + lane] + red[448 + lane]);
+  const float ctr = on && wsum > 0.f ? sum * (1.0f / wsum) : 0.f;
+  if (wave == 0) hdr[2 * M16 + cc] = ctr;  // cN[c] (cc < C), then cS[c]
+#pragma unroll
+  for (int k = 0; k < 16; ++k)
+    if (k < per)
+      *reinterpret_cast<T*>(img + g.OFF_2 + lds_off(j0 + k, cc * g.SZ, g.WROW)) =
+          from_f<T>(on && j0 + k < M ? v[k] - ctr : 0.f);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_prep_back(PrepGeo g, PrepArgs p) {
+  __shared__ float red[512];
   if (gridDim.y > 1) {
     p.A = head_at(p.A, p.hs_A);
     p.b = head_at(p.b, p.hs_b);
@@ -177,61 +166,24 @@ __global__ void __launch_bounds__(256) k_prep(PrepGeo g, PrepArgs p) {
     p.dS = head_at(p.dS, p.hs_dS);
     p.img = head_at(p.img, p.hs_img);
   }
-  const bool back = p.pass == kSliceBwd || p.pass == kWeightsBwd;
-  const int nback = back ? g.M + (2 * g.C + 255) / 256 : 0;
-  if ((int)blockIdx.x < nback) {
-    prep_back<T>(g, p, blockIdx.x, red);
-    return;
-  }
-  char* img = reinterpret_cast<char*>(p.img);
-  const T* A = reinterpret_cast<const T*>(p.A);
-  const T* av = reinterpret_cast<const T*>(p.a);
-  const int C = g.C, M = g.M, M16 = g.M16, cr = p.cr;
-  const int64_t tid = (int64_t)(blockIdx.x - nback) * blockDim.x + threadIdx.x;
-  const int64_t nth = (int64_t)(gridDim.x - nback) * blockDim.x;
-
-  float* hdr = reinterpret_cast<float*>(img);
-  if (p.pass == kDesliceW) {  // the stored-weights deslice: its S'^T table only
-    prep_deslice_table<T>(g, p, img, tid, nth);
-    return;
-  }
-  // padded slices j >= M get bias -inf: their softmax weight is exactly 0
-  for (int64_t j = tid; j < M16; j += nth) hdr[j] = j < M ? (p.b ? p.b[j] : 0.f) : -INFINITY;
-  if (!back)
-    for (int64_t k = tid; k < 2 * M16 + 2 * C; k += nth) hdr[M16 + k] = 0.f;  // dden, cN, cS, sw
-  for (int64_t c = tid; c < C; c += nth)
-    hdr[3 * M16 + 2 * C + c] = av && c < cr ? to_f<T>(av[c]) : 0.f;
-  // logits table: rows j < M16: A[:, j] (0 beyond M); row M16: a (columns
-  // c >= cr: 0)
-  const int64_t nL = (int64_t)(M16 + 1) * C;
-#pragma unroll 4
-  for (int64_t k = tid; k < nL; k += nth) {
-    const int j = (int)(k / C), c = (int)(k - (int64_t)j * C);
-    T v;
-    if (c >= cr)
-      v = from_f<T>(0.f);
-    else if (j < M16)
-      v = j < M ? A[(int64_t)c * M + j] : from_f<T>(0.f);
-    else
-      v = av ? av[c] : from_f<T>(0.f);
-    *reinterpret_cast<T*>(img + g.OFF_L + lds_off(j, c * g.SZ, g.TROW)) = v;
-  }
-  if (p.pass == kDeslice) prep_deslice_table<T>(g, p, img, tid, nth);
+  if ((int)blockIdx.x <= g.M16)
+    prep_row<T>(g, p, blockIdx.x, red);
+  else
+    prep_columns<T>(g, p, blockIdx.x - g.M16 - 1, red);
 }
 
-hipError_t launch_prep(const PrepArgs& p, hipStream_t st) {
-  if (!p.img || (!p.A && p.pass != kDesliceW)) return hipErrorInvalidValue;
-  if (p.cr < 16 || p.cr > p.C || p.cr % 16) return hipErrorInvalidValue;
-  if ((p.pass == kDeslice || p.pass == kDesliceW) && !p.Sp) return hipErrorInvalidValue;
+hipError_t launch_prep_back(const PrepArgs& p, hipStream_t st) {
+  if (!p.img || !p.A || (p.pass != kSliceBwd && p.pass != kWeightsBwd)) return hipErrorInvalidValue;
+  if (p.cr < 16 || p.cr > p.C || p.cr % 16 || p.C > 256 || p.C % 32) return hipErrorInvalidValue;
+  if (p.M < 1 || p.M > 16 * p.MB || p.MB > 4) return hipErrorInvalidValue;
   if (p.pass == kSliceBwd && p.dS && (!p.num || !p.den)) return hipErrorInvalidValue;
-  PrepGeo g = prep_geo(p.dtype, p.C, p.M, p.MB);
-  const bool back = p.pass == kSliceBwd || p.pass == kWeightsBwd;
   if (p.heads < 1 || p.heads > kMaxHeads) return hipErrorInvalidValue;
-  const int blocks = 64 + (back ? p.M + (2 * p.C + 255) / 256 : 0);
+  const PrepGeo g = prep_geo(p.dtype, p.C, p.M, p.MB);
+  const dim3 grid(g.M16 + 1 + 2 * p.C / 64, p.heads);
   if (p.dtype == 1)
-    hipLaunchKernelGGL(k_prep<bf16>, dim3(blocks, p.heads), dim3(256), 0, st, g, p);
+    hipLaunchKernelGGL(k_prep_back<bf16>, grid, dim3(256), 0, st, g, p);
   else
-    hipLaunchKernelGGL(k_prep<float>, dim3(blocks, p.heads), dim3(256), 0, st, g, p);
+    hipLaunchKernelGGL(k_prep_back<float>, grid, dim3(256), 0, st, g, p);
   return hipGetLastError();
 }
 
@@ -239,43 +191,68 @@ hipError_t launch_prep(const PrepArgs& p, hipStream_t st) {
 // Ordered reduction of partial records (and the states of Eq. 1)
 // ---------------------------------------------------------------------------
 // Fixed-order sum of the 16 group sums of one column.
-__device__ __forceinline__ float group_total(const double (&t16)[16]) {
+__device__ __forceinline__ float group_total(const double* t16) {
   double t[8];
 #pragma unroll
   for (int q = 0; q < 8; ++q) t[q] = t16[2 * q] + t16[2 * q + 1];
   return (float)(((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7])));
 }
 
-__global__ void k_reduce(const float* __restrict__ parts, int P, int64_t rec, Segments seg) {
-  // 16 record columns x 16 partial groups per block: each thread adds every
-  // 16th partial (few dependent loads per thread), then the 16 group sums
-  // are added in a fixed tree order.  The sums are formed in fp64: the
-  // records are signed partial sums (gradients) whose total can be far
-  // smaller than the sum of their magnitudes.  A block of numerator columns
-  // (16 columns of one slice j, as 16 divides C) also forms den_j, in the
-  // same order as den_j's own block, for the states.
-  __shared__ double sh[17][16];
+// Bound by latency (8 MB of records at C = 256, M = 32, one block of kRedCols
+// columns per CU): 32 record columns x 16 partial groups per block, each
+// thread adding every 16th partial with all of a chunk's loads (256 records)
+// issued at once.  (Before, with 16 columns and a loop of batches of 8 whose
+// remainder ran load by load: 5 to 7 us per call, most of it the remainder
+// for fewer than 128 records.)
+constexpr int kRedCols = 32;
+
+// Sum over records pg, pg + 16, .. of one column, in that order.
+__device__ __forceinline__ void red_chunk(float (&v)[16], const float* col, int64_t rec, int p0,
+                                          int pg, int P) {
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    v[u] = 0.f;
+    if (p0 + 16 * u < P) {  // (uniform; records past the end: the last one, not added)
+      const int p = p0 + 16 * u + pg;
+      v[u] = col[(int64_t)(p < P ? p : P - 1) * rec];
+    }
+  }
+}
+__device__ __forceinline__ double red_add(double acc, const float (&v)[16], int p0, int pg, int P) {
+#pragma unroll
+  for (int u = 0; u < 16; ++u) acc += p0 + 16 * u + pg < P ? (double)v[u] : 0.0;
+  return acc;
+}
+
+__global__ void __launch_bounds__(16 * kRedCols) k_reduce(const float* __restrict__ parts, int P,
+                                                          int64_t rec, Segments seg) {
+  // The 16 group sums of a column are added in a fixed tree order.  The sums
+  // are formed in fp64: the records are signed partial sums (gradients) whose
+  // total can be far smaller than the sum of their magnitudes.  Sixteen
+  // numerator columns belong to one slice j (16 divides C): their threads also
+  // form den_j, in the same order as den_j's own block, for the states.
+  __shared__ double sh[kRedCols][17];
+  __shared__ double shd[kRedCols / 16][17];
   // head blockIdx.y of a per-head batch (0 otherwise): its records and
   // destinations at the batch's strides, applied where they are used (the
   // argument struct is only read: writing its arrays would copy it to scratch)
   parts = head_at(parts, seg.hs_parts);
   float* const S = head_at(seg.S, seg.hs_S);
-  const int kk = threadIdx.x & 15, pg = threadIdx.x >> 4;
-  const int64_t k0 = (int64_t)blockIdx.x * 16, k = k0 + kk;
+  const int kk = threadIdx.x % kRedCols, pg = threadIdx.x / kRedCols, h = kk / 16;
+  const int64_t k0 = (int64_t)blockIdx.x * kRedCols, k = k0 + kk;
+  const int64_t kc = k < rec ? k : rec - 1;
   const bool states = S != nullptr && k0 < seg.nS;
-  double acc = 0.0;
-  if (k < rec) {
-#pragma unroll 8
-    for (int p = pg; p < P; p += 16) acc += (double)parts[(int64_t)p * rec + k];
+  const int64_t kd = states ? seg.den_col + (kc < seg.nS ? kc : seg.nS - 1) / seg.C : 0;
+  double acc = 0.0, ad = 0.0;
+  for (int p0 = 0; p0 < P; p0 += 256) {
+    float v[16], w[16];
+    red_chunk(v, parts + kc, rec, p0, pg, P);
+    if (states) red_chunk(w, parts + kd, rec, p0, pg, P);
+    acc = red_add(acc, v, p0, pg, P);
+    if (states) ad = red_add(ad, w, p0, pg, P);
   }
   sh[kk][pg] = acc;
-  if (states && kk == 0) {
-    const int64_t dc = seg.den_col + k0 / seg.C;
-    double ad = 0.0;
-#pragma unroll 8
-    for (int p = pg; p < P; p += 16) ad += (double)parts[(int64_t)p * rec + dc];
-    sh[16][pg] = ad;
-  }
+  if (states && kk % 16 == 0) shd[h][pg] = ad;
   __syncthreads();
   if (pg == 0 && k < rec) {
     const float tot = group_total(sh[kk]);
@@ -289,7 +266,7 @@ __global__ void k_reduce(const float* __restrict__ parts, int P, int64_t rec, Se
       off -= seg.len[i];
     }
     if (states && k < seg.nS) {
-      const float den = group_total(sh[16]);
+      const float den = group_total(shd[h]);
       S[k] = tot / (den >= seg.eps ? den : seg.eps);
     }
   }
@@ -303,8 +280,8 @@ hipError_t launch_reduce(const float* partials, int P, int64_t rec, const Segmen
     return hipErrorInvalidValue;
   const int heads = seg.heads > 1 ? seg.heads : 1;
   if (heads > kMaxHeads) return hipErrorInvalidValue;
-  const int blocks = (int)((rec + 15) / 16);
-  hipLaunchKernelGGL(k_reduce, dim3(blocks, heads), dim3(256), 0, st, partials, P, rec, seg);
+  const int blocks = (int)((rec + kRedCols - 1) / kRedCols);
+  hipLaunchKernelGGL(k_reduce, dim3(blocks, heads), dim3(16 * kRedCols), 0, st, partials, P, rec, seg);
   return hipGetLastError();
 }
 

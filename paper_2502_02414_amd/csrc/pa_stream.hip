@@ -34,9 +34,13 @@ hipError_t launch_stream(int pass, int dtype, int C, int MB, const StreamLaunch&
   // never a device fault)
   // (the stored-weights passes read W, given as G, in place of x and G)
   const bool win = pass == kDesliceW || pass == kDesliceBwdW;
-  if ((win ? !L.G : !L.x) || !L.img || L.N < 1 || L.M < 1 || L.M > 16 * MB || L.P < 1 ||
+  if ((win ? !L.G : !L.x) || L.N < 1 || L.M < 1 || L.M > 16 * MB || L.P < 1 ||
       L.cr < 16 || L.cr > C || L.cr % 16)
     return hipErrorInvalidValue;
+  // the tables: an image for the backward passes, A and S' for the others
+  const bool back = pass == kSliceBwd || pass == kWeightsBwd;
+  if (back ? !L.img : !win && !L.tab.A) return hipErrorInvalidValue;
+  if ((pass == kDeslice || pass == kDesliceW) && !L.tab.Sp) return hipErrorInvalidValue;
   const bool reduces = agg_fwd(pass) || agg_bwd(pass) || pass == kSliceBwd || pass == kWeightsBwd;
   if (reduces && !L.partials) return hipErrorInvalidValue;
   if ((pass == kDeslice || pass == kDesliceW || pass == kWeights || pass == kSliceBwd ||
@@ -46,7 +50,7 @@ hipError_t launch_stream(int pass, int dtype, int C, int MB, const StreamLaunch&
   if (pass == kSliceBwd && L.deslice && !L.dY) return hipErrorInvalidValue;
   if (pass == kWeightsBwd && !L.dW) return hipErrorInvalidValue;
   StreamArgs a;
-  a.x = L.x; a.G = L.G; a.dY = L.dY; a.img = L.img; a.out = L.out; a.tau_out = L.tau_out;
+  a.x = L.x; a.G = L.G; a.dY = L.dY; a.tab = L.tab; a.img = L.img; a.out = L.out; a.tau_out = L.tau_out;
   a.dW = L.dW; a.dtau = L.dtau; a.partials = L.partials; a.N = L.N; a.M = L.M; a.cr = L.cr;
   a.rec = L.rec;
   a.tb = L.tb; a.tb_dev = L.tb_dev; a.tau_min = L.tau_min;
@@ -54,7 +58,8 @@ hipError_t launch_stream(int pass, int dtype, int C, int MB, const StreamLaunch&
   if (L.heads < 1 || L.heads > kMaxHeads) return hipErrorInvalidValue;
   a.heads = L.heads;
   a.hs_x = L.hs_x; a.hs_g = L.hs_g; a.hs_dy = L.hs_dy; a.hs_out = L.hs_out;
-  a.hs_img = L.hs_img; a.hs_part = L.hs_part; a.hs_tb = L.hs_tb;
+  a.hs_part = L.hs_part; a.hs_tb = L.hs_tb;
+  a.hs_A = L.hs_A; a.hs_b = L.hs_b; a.hs_a = L.hs_a; a.hs_Sp = L.hs_Sp; a.hs_img = L.hs_img;
   switch (pass) {
     case kAggregate: return launch_aggregate_pass(dtype, C, MB, a, L.P, st);
     case kDeslice: return launch_deslice_pass(dtype, C, MB, a, L.P, st);

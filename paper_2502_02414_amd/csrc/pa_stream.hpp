@@ -35,6 +35,7 @@
 #include "pa_device.hpp"
 #include "pa_internal.h"
 #include "pa_layout.h"
+#include "pa_tables.hpp"
 
 namespace pa {
 
@@ -42,7 +43,8 @@ struct StreamArgs {
   const void* x;
   const void* G;
   const void* dY;        // kDesliceBwd, kSliceBwd (deslice term)
-  const void* img;       // table image (workspace)
+  TableSrc tab;          // what the block's tables are built from (forward tables)
+  const void* img;       // table image (workspace; the backward passes)
   void* out;             // y, dx (dtype) or W (fp32)
   float* tau_out;        // kWeights (nullable)
   const float* dW;       // kWeightsBwd
@@ -57,7 +59,8 @@ struct StreamArgs {
   int flags;
   // per-head batch (see StreamLaunch)
   int heads;
-  int64_t hs_x, hs_g, hs_dy, hs_out, hs_img, hs_part, hs_tb;
+  int64_t hs_x, hs_g, hs_dy, hs_out, hs_part, hs_tb;
+  int64_t hs_A, hs_b, hs_a, hs_Sp, hs_img;
   int cr;                // channels of the point rows (<= C, a multiple of 16)
 };
 
@@ -108,6 +111,10 @@ __device__ __forceinline__ void head_offsets(StreamArgs& a) {
   a.G = head_ptr(a.G, a.hs_g);
   a.dY = head_ptr(a.dY, a.hs_dy);
   a.out = head_ptr(a.out, a.hs_out);
+  a.tab.A = head_ptr(a.tab.A, a.hs_A);
+  a.tab.b = head_ptr(a.tab.b, a.hs_b);
+  a.tab.a = head_ptr(a.tab.a, a.hs_a);
+  a.tab.Sp = head_ptr(a.tab.Sp, a.hs_Sp);
   a.img = head_ptr(a.img, a.hs_img);
   a.partials = head_ptr(a.partials, a.hs_part);
   a.tb_dev = head_ptr(a.tb_dev, a.hs_tb);
@@ -890,7 +897,7 @@ k_aggregate(StreamArgs a) {
   float bias[MB][4];
   auto init = [&]() {
     if constexpr (!WIN) {
-      copy_image<G_::img_bytes(PASS), 64 * WAVES>(smem, a.img);
+      build_logits<T, C, MB, 64 * WAVES>(smem, a.tab, a.M, a.cr);
       __syncthreads();
     }
     zero_lds(gbuf, 2 * H * G_::GT);
@@ -1008,7 +1015,7 @@ k_aggregate(StreamArgs a) {
     if constexpr (!WIN) load_tile<T, C, ROWS, NT, EX>(st.x, X, p0, a.N, a.cr);
     if constexpr (BWD) load_tile<T, C, ROWS, NT, EX>(st.y, Y, p0, a.N, a.cr);
     // G (or W): streamed either way; `safe` is any readable 16 bytes
-    const void* safe = WIN ? a.img : static_cast<const void*>(X);
+    const void* safe = WIN ? a.dY : static_cast<const void*>(X);
     load_g<T, MB, ROWS, true>(st.g, Gp, safe, p0, a.N, a.M, hasG);
   };
   auto store = [&](const Stage& st) {
@@ -1087,10 +1094,8 @@ k_deslice(StreamArgs a) {
 
   float bias[MB][4];
   auto init = [&]() {
-    if constexpr (WIN)  // the deslice table part of the image only
-      copy_image<G_::SZ_S, 64 * WAVES>(smem, reinterpret_cast<const char*>(a.img) + G_::OFF_2);
-    else
-      copy_image<G_::img_bytes(kDeslice), 64 * WAVES>(smem, a.img);
+    if constexpr (!WIN) build_logits<T, C, MB, 64 * WAVES>(smem, a.tab, a.M, a.cr);
+    build_deslice<T, C, MB, 64 * WAVES>(smem + (WIN ? 0 : G_::OFF_2), a.tab, a.M, a.cr);
     __syncthreads();
     zero_lds(gt, G_::GT);
 #pragma unroll
@@ -1110,7 +1115,7 @@ k_deslice(StreamArgs a) {
   auto load = [&](Stage& st, int64_t tile) {
     constexpr bool NT = !keep_loads<PASS>();
     if constexpr (WIN) {
-      load_g<T, MB, 16, NT>(st.g, Gp, a.img, tile * 16, a.N, a.M, hasG);
+      load_g<T, MB, 16, NT>(st.g, Gp, a.tab.Sp, tile * 16, a.N, a.M, hasG);
     } else {
       load_tile<T, C, 16, NT, EX>(st.x, X, tile * 16, a.N, a.cr);
       load_g<T, MB, 16, NT>(st.g, Gp, X, tile * 16, a.N, a.M, hasG);
@@ -1195,7 +1200,7 @@ __global__ void __launch_bounds__((64 * Geo<sizeof(T), C, MB>::waves(kWeights)))
   const int r = lane_id() & 15, g = lane_id() >> 4;
   const bool hasG = a.flags & kHasG;
 
-  copy_image<G_::img_bytes(kWeights), 64 * WAVES>(smem, a.img);
+  build_logits<T, C, MB, 64 * WAVES>(smem, a.tab, a.M, a.cr);
   __syncthreads();
   const char* tabL = smem + G_::OFF_L;
   char* xt = smem + G_::img_bytes(kWeights) + wave * G_::wave_bytes(kWeights);
