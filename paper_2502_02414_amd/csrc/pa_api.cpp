@@ -64,9 +64,8 @@ Layout layout_of(const pa_dims& d) {
   const int64_t rec = (int64_t)d.C * d.M + d.M + d.C + 1;  // the largest record
   const int P = pa::kPartialsMax;
   const size_t mc = (size_t)d.M * d.C;
-  // token scratch: eight [M,C] matrices in double (fp32 storage) or float,
-  // and the attention matrices of the heads
-  const size_t attn = (16 * mc + (size_t)d.H * d.M * d.M) * sizeof(float);
+  // token scratch: eight [M,C] matrices in double (fp32 storage) or float
+  const size_t attn = 16 * mc * sizeof(float);
   L.img = 0;
   L.parts = up(pa::image_bytes(d.dtype, cpad(d.C), mblocks(d.M)));
   L.attn = L.parts + up((size_t)P * rec * sizeof(float));
@@ -491,7 +490,7 @@ static pa_status check_attn(const pa_dims* dims, const float* S, const pa_attn_p
 
 namespace {
 struct AttnWs {
-  float *Q, *K, *V, *O, *dO, *dQ, *dK, *dV, *P;
+  float *Q, *K, *V, *O, *dO, *dQ, *dK, *dV, *Vf;
 };
 AttnWs attn_ws(const pa_dims& d, void* ws) {
   const size_t mc = (size_t)d.M * d.C;
@@ -499,25 +498,26 @@ AttnWs attn_ws(const pa_dims& d, void* ws) {
   AttnWs a;
   a.Q = base; a.K = base + mc; a.V = base + 2 * mc; a.O = base + 3 * mc;
   a.dO = base + 4 * mc; a.dQ = base + 5 * mc; a.dK = base + 6 * mc; a.dV = base + 7 * mc;
-  a.P = base + 8 * mc;
+  a.Vf = base + 8 * mc;
   return a;
 }
 
-// General path (heads too large for the fused kernel): Q, K, V, P, O in the
-// workspace, O -> Sp when Sp is wanted and there is no output projection.
-pa_status attn_forward_general(const pa_dims& d, const float* S, const pa_attn_params* ap,
-                               float* Sp, const AttnWs& w, hipStream_t st) {
-  const int M = d.M, C = d.C;
+// Q, K, V = S W + b into the workspace (more products may be added to q).
+pa::Proj qkv_proj(const pa_dims& d, const float* S, const pa_attn_params* ap, const AttnWs& w) {
   pa::Proj q{};
-  q.n = 3; q.M = M; q.Cin = C; q.Cout = C;
+  q.n = 3; q.M = d.M; q.Cin = d.C; q.Cout = d.C;
   q.in[0] = q.in[1] = q.in[2] = S;
   q.W[0] = ap->Wq; q.W[1] = ap->Wk; q.W[2] = ap->Wv;
   q.b[0] = ap->bq; q.b[1] = ap->bk; q.b[2] = ap->bv;
   q.out[0] = w.Q; q.out[1] = w.K; q.out[2] = w.V;
-  PA_HIP(pa::launch_proj(q, st), "QKV projection");
-  float* O = (ap->Wo || !Sp) ? w.O : Sp;
-  PA_HIP(pa::launch_attn_core(w.Q, w.K, w.V, w.P, O, M, C, d.H, st), "attention core");
-  return PA_OK;
+  return q;
+}
+
+pa::CoreArgs core_args(const pa_dims& d, const AttnWs& w) {
+  pa::CoreArgs a{};
+  a.Q = w.Q; a.K = w.K; a.V = w.V;
+  a.M = d.M; a.C = d.C; a.H = d.H;
+  return a;
 }
 
 // Double-precision token forward (fp32 storage): S' feeds the slice
@@ -583,15 +583,6 @@ pa_status attn64_forward(const pa_dims& d, const float* S, const pa_attn_params*
   PA_HIP(pa::launch_mm64(b, st), "output projection (double)");
   return PA_OK;
 }
-
-pa::HeadArgs head_args(const pa_dims& d, const float* S, const pa_attn_params* ap) {
-  pa::HeadArgs h{};
-  h.S = S;
-  h.W[0] = ap->Wq; h.W[1] = ap->Wk; h.W[2] = ap->Wv;
-  h.b[0] = ap->bq; h.b[1] = ap->bk; h.b[2] = ap->bv;
-  h.geo.M = d.M; h.geo.C = d.C; h.geo.H = d.H;
-  return h;
-}
 }  // namespace
 
 pa_status pa_token_attention(const pa_dims* dims, const float* S, const pa_attn_params* ap,
@@ -603,15 +594,10 @@ pa_status pa_token_attention(const pa_dims* dims, const float* S, const pa_attn_
   const pa_dims& d = *dims;
   if (d.dtype == PA_F32) return attn64_forward(d, S, ap, Sp, ws, st);
   const AttnWs w = attn_ws(d, ws);
-  // the heads' output: straight to Sp without an output projection
-  float* O = ap->Wo ? w.O : Sp;
-  if (pa::head_fits(d.M, d.C, d.H)) {
-    pa::HeadArgs h = head_args(d, S, ap);
-    h.O = O;
-    PA_HIP(pa::launch_head(h, false, st), "attention heads");
-  } else {
-    PA_TRY(attn_forward_general(d, S, ap, Sp, w, st));
-  }
+  PA_HIP(pa::launch_proj(qkv_proj(d, S, ap, w), st), "QKV projection");
+  pa::CoreArgs c = core_args(d, w);
+  c.O = ap->Wo ? w.O : Sp;  // straight to Sp without an output projection
+  PA_HIP(pa::launch_core(c, false, st), "attention core");
   if (ap->Wo) {
     pa::Proj o{};
     o.n = 1; o.M = d.M; o.Cin = d.C; o.Cout = d.C;
@@ -637,26 +623,30 @@ pa_status pa_token_attention_backward(const pa_dims* dims, const float* S,
   const pa_dims& d = *dims;
   const int M = d.M, C = d.C;
   const AttnWs w = attn_ws(d, ws);
-  const float* dO = dSp;
-  if (ap->Wo) {
-    pa::Proj q{};  // dO = dSp Wo^T
-    q.n = 1; q.M = M; q.Cin = C; q.Cout = C; q.transW = 1;
-    q.in[0] = dSp; q.W[0] = ap->Wo; q.out[0] = w.dO;
-    PA_HIP(pa::launch_proj(q, st), "dO");
-    dO = w.dO;
-  }
+  // Q, K, V again and dO = dSp Wo^T in one launch, then the heads.  The tokens
+  // are nearly equal, and the chain rule sees only the differences of K's and
+  // of V's rows: they are projected from the states minus state 0 (no bias),
+  // which keeps the rounding relative to the differences.  O = P V (for dWo)
+  // takes V itself.
   const bool wantWo = ag && ap->Wo && (ag->dWo || ag->dbo);
-  if (pa::head_fits(M, C, d.H)) {
-    pa::HeadArgs h = head_args(d, S, ap);  // recomputes the forward per head
-    h.dO = dO;
-    h.O = wantWo ? w.O : nullptr;
-    h.dX[0] = w.dQ; h.dX[1] = w.dK; h.dX[2] = w.dV;
-    PA_HIP(pa::launch_head(h, true, st), "attention heads backward");
-  } else {
-    PA_TRY(attn_forward_general(d, S, ap, nullptr, w, st));  // Q, K, V, P, O
-    PA_HIP(pa::launch_attn_core_bwd(w.Q, w.K, w.V, w.P, dO, w.dQ, w.dK, w.dV, M, C, d.H, st),
-           "attention core backward");
+  pa::Proj q = qkv_proj(d, S, ap, w);
+  q.center[1] = q.center[2] = 1;
+  q.b[1] = q.b[2] = nullptr;
+  if (ap->Wo) {
+    q.in[3] = dSp; q.W[3] = ap->Wo; q.out[3] = w.dO; q.transW[3] = 1;
+    q.n = 4;
   }
+  if (wantWo) {
+    q.in[4] = S; q.W[4] = ap->Wv; q.b[4] = ap->bv; q.out[4] = w.Vf;
+    q.n = 5;
+  }
+  PA_HIP(pa::launch_proj(q, st), "QKV projection and dO");
+  pa::CoreArgs c = core_args(d, w);
+  c.Vf = w.Vf;
+  c.dO = ap->Wo ? w.dO : dSp;
+  c.O = wantWo ? w.O : nullptr;
+  c.dQ = w.dQ; c.dK = w.dK; c.dV = w.dV;
+  PA_HIP(pa::launch_core(c, true, st), "attention core backward");
   // dS = dQ Wq^T + dK Wk^T + dV Wv^T; dW = S^T dX, db = 1^T dX; dWo = O^T dSp
   pa::GradArgs g{};
   g.M = M; g.C = C;
@@ -671,6 +661,8 @@ pa_status pa_token_attention_backward(const pa_dims* dims, const float* S,
     for (int t = 0; t < 4; ++t) {
       if (!dW4[t] && !db4[t]) continue;
       if (t == 3 && !ap->Wo) continue;
+      // (sum_j dK_j = 0: dWk is that of the states minus state 0 as well)
+      g.center[g.nO] = t == 1;
       g.A[g.nO] = A4[t]; g.B[g.nO] = B4[t]; g.dW[g.nO] = dW4[t]; g.db[g.nO] = db4[t];
       ++g.nO;
     }

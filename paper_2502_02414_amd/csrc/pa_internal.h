@@ -106,52 +106,48 @@ struct Segments {
 hipError_t launch_reduce(const float* partials, int P, int64_t rec, const Segments& seg,
                          hipStream_t st);
 
-// Token-side products (fp32, M <= 64 rows):
-//   sum = 0: out_p [M,Cout] = in_p [M,Cin] op(W_p) + b_p   for p < n
-//   sum = 1: out_0 [M,Cout] = sum_p in_p op(W_p) + b_0
-//   op(W) = W ([Cin,Cout]) or, with transW, W^T (W given as [Cout,Cin]).
+// Token-side products (fp32, M <= 64 rows), p < n in one launch:
+//   out_p [M,Cout] = in_p [M,Cin] op(W_p) + b_p
+//   op(W) = W ([Cin,Cout]) or, with transW, W^T (W given as [Cout,Cin]);
+//   with center, row 0 of in_p is subtracted from its rows first.
+constexpr int kProjMax = 5;
 struct Proj {
-  const float* in[3];
-  const float* W[3];
-  const float* b[3];
-  float* out[3];
-  int n, M, Cin, Cout, transW, sum;
+  const float* in[kProjMax];
+  const float* W[kProjMax];
+  const float* b[kProjMax];
+  float* out[kProjMax];
+  int transW[kProjMax];
+  int center[kProjMax];
+  int n, M, Cin, Cout;
 };
 hipError_t launch_proj(const Proj& q, hipStream_t st);
-// Fused per-head token attention (one block per head, channels [hD, hD+D)):
-//   forward:  O_h = softmax(Q_h K_h^T / sqrt(D)) V_h with [Q|K|V]_h = S W_h + b_h
-//   backward: the same forward, then dQ_h, dK_h, dV_h from dO_h (and O_h if
-//             O is given).
-// M, C, H are set by the caller; launch_head fills the rest of the geometry
-// and returns hipErrorInvalidConfiguration when a head does not fit on chip
-// (head_fits tells beforehand).
-struct HeadGeo {
-  int M, C, H, D;
-  int M16, D16, MT, NT, T;  // padded rows / head columns, projection tiles
-  int KC, SR;               // K chunk, chunk row stride (floats)
-  size_t lds;
+// Attention cores of all heads (channels [hD, hD + D), D = C / H) from Q, K, V
+// [M,C]:
+//   forward:  O_h = softmax(Q_h K_h^T / sqrt(D)) V_h
+//   backward: dQ_h, dK_h, dV_h from dO_h (and O_h = P_h Vf_h if O is given);
+//             K and V may be given up to a row common to all states (the
+//             softmax and its chain rule do not see it).
+struct CoreArgs {
+  const float *Q, *K, *V;
+  const float* Vf;      // [M,C] (backward with O)
+  const float* dO;      // [M,C] (backward)
+  float* O;             // [M,C] forward output; backward: nullable
+  float *dQ, *dK, *dV;  // [M,C] (backward)
+  int M, C, H;
 };
-struct HeadArgs {
-  const float* S;     // [M,C]
-  const float* W[3];  // Wq, Wk, Wv [C,C]
-  const float* b[3];  // [C], nullable
-  const float* dO;    // [M,C] (backward)
-  float* O;           // [M,C] forward output; backward: nullable
-  float* dX[3];       // dQ, dK, dV [M,C] (backward)
-  HeadGeo geo;
-};
-bool head_fits(int M, int C, int H);
-hipError_t launch_head(HeadArgs a, bool bwd, hipStream_t st);
+hipError_t launch_core(const CoreArgs& a, bool bwd, hipStream_t st);
 // Parameter-side products of the token backward, one launch:
 //   dS = sum_{p < nS} X_p W_p^T           (X_p [M,C], W_p [C,C]; dS [M,C])
 //   dW_p = A_p^T B_p, db_p = 1^T B_p      (p < nO; A_p, B_p [M,C]; NULL
-//                                          outputs skipped)
+//                                          outputs skipped; with center, row 0
+//                                          of A_p is subtracted from its rows)
 struct GradArgs {
   const float* X[3];
   const float* W[3];
   int nS;
   float* dS;
   const float* A[4];
+  int center[4];
   const float* B[4];
   float* dW[4];
   float* db[4];
@@ -159,14 +155,6 @@ struct GradArgs {
   int M, C;
 };
 hipError_t launch_token_grads(const GradArgs& a, hipStream_t st);
-// Per-head attention core: P_h = softmax(Q_h K_h^T * scale), O_h = P_h V_h.
-hipError_t launch_attn_core(const float* Q, const float* K, const float* V, float* P, float* O,
-                            int M, int C, int H, hipStream_t st);
-// Per-head attention backward core: from dO, P, Q, K, V -> dQ, dK, dV.
-hipError_t launch_attn_core_bwd(const float* Q, const float* K, const float* V,
-                                const float* P, const float* dO, float* dQ, float* dK,
-                                float* dV, int M, int C, int H, hipStream_t st);
-
 // Small products in double precision (pa_tokens64.hip): the token attention
 // forward of fp32 storage and the Project folding.
 // Operand element (i, k) = p[i rs + k cs], fp32 or fp64; p == NULL: all ones.

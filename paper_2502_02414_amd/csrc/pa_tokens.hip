@@ -1,752 +1,348 @@
 // Token side of the layer (gfx950): attention among the M <= 64 physical
-// states (Eq. 2) and its backward.  These products are tiny (M x C by C x C
-// at most); what costs is latency and the number of launches, so the layer's
-// token step is one launch per head-parallel part:
-//   k_head_fwd   per head h (channels [hD, hD + D)): Q_h, K_h, V_h = S W_h +
-//                b_h, P_h = softmax(Q_h K_h^T / sqrt(D)), O_h = P_h V_h
-//   k_head_bwd   per head: the same forward, then dV_h, dQ_h, dK_h
+// states (Eq. 2) and its backward, in fp32 (the fp32-storage forward runs in
+// double, pa_tokens64.hip).  These products are tiny (M x C by C x C at most)
+// and bound by latency: a kernel is one round of loads, a short MFMA chain
+// (v_mfma_f32_16x16x4_f32) and its stores, and the work is spread over as many
+// CUs as it has 16 x 16 tiles.
+//   k_proj         out_p = In_p op(W_p) + b_p (op = W or W^T): a block per tile
+//   k_core         per head h (channels [hD, hD + D)) and 16 query rows, one
+//                  wave: P_h = softmax(Q_h K_h^T / sqrt(D)), O_h = P_h V_h
+//   k_core_bwd     per head: the same P_h, then dV_h, dQ_h, dK_h (and O_h)
 //   k_token_grads  dS = sum_p dX_p W_p^T, dW_p = A_p^T B_p, db_p = 1^T B_p,
-//                every output tile of every product in one launch
-// The head kernels run the projections (3 M x C x D contractions) on
-// v_mfma_f32_16x16x4f32 from LDS and the core from LDS.  Shapes whose head
-// does not fit on chip use the general kernels:
-//   k_proj       out_p = In_p op(W_p) + b_p  (op = W or W^T; or the sum over p)
-//   k_attn_core / k_attn_core_bwd  the core of one head from global Q, K, V
+//                  every output tile of every product in one launch
+// (One block per head for projections and core together, staged through LDS,
+// took 13 us forward and 15 us backward at M = 32, C = 256, H = 8, and 22 and
+// 29 us at M = 64; the projections and the core apart take about 4 + 4 and 4 +
+// 6 us, and serve every head width.)
 #include "pa_device.hpp"
 #include "pa_internal.h"
+#include "pa_layout.h"
 
 namespace pa {
-
-constexpr int kThreads = 256;  // every token-side kernel runs 256 threads
-
-// Stage n elements with all of a thread's loads in flight before its
-// stores: ld(e) must be valid for every e < n (callers clamp), st(e, v)
-// writes element e.
-template <int NB, typename Ld, typename St>
-__device__ __forceinline__ void staged(int n, Ld&& ld, St&& st) {
-  for (int base = threadIdx.x; base < n; base += NB * kThreads) {
-    float v[NB];
-#pragma unroll
-    for (int u = 0; u < NB; ++u) {
-      const int e = base + u * kThreads;
-      v[u] = ld(e < n ? e : n - 1);
-    }
-#pragma unroll
-    for (int u = 0; u < NB; ++u) {
-      const int e = base + u * kThreads;
-      if (e < n) st(e, v[u]);
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// k_proj: one block per 16 token rows x 32 output columns (of one product,
-// or of the sum over products; the last block of columns may hold 16).  The
-// block's rows of In (transposed to [k][row]) and its 32 columns of op(W)
-// (zero past Cout) are staged in LDS; the 4 waves split K into quarters,
-// each lane accumulating 2 rows x 4 columns, and the quarters are added in
-// wave order.
-// ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_proj(Proj q) {
-  extern __shared__ __attribute__((aligned(16))) float sm[];
-  const int M = q.M, Cin = q.Cin, Cout = q.Cout;
-  float* in_s = sm;               // [Cin][16]
-  float* w_s = sm + Cin * 16;     // [Cin][32]
-  float* red = w_s + Cin * 32;    // [4 waves][16][32]
-  const int j0 = blockIdx.x * 32, r0 = blockIdx.y * 16;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int cg = lane & 7, rp = lane >> 3;  // columns 4cg..+3, rows 2rp, 2rp+1
-  const int kq = Cin / 4, kb = wave * kq;
-  float acc[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-  const int p0 = q.sum ? 0 : blockIdx.z, p1 = q.sum ? q.n : blockIdx.z + 1;
-  for (int p = p0; p < p1; ++p) {
-    const float* in = q.in[p];
-    const float* W = q.W[p];
-    // In rows r0..r0+15 (zero past M; stored transposed) and 32 columns of
-    // op(W), as float4 along the contiguous dimension: every load of the
-    // thread is issued before its LDS stores (one memory round trip)
-    const int ci4 = Cin / 4;
-    float4 vi[4], vw[8];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = threadIdx.x + 256 * u;  // < 16 * ci4 = 4 Cin <= 1024
-      const int r = e & 15, k4 = e >> 4;    // consecutive threads: consecutive LDS words
-      const int rr = r0 + r < M ? r0 + r : M - 1;
-      if (e < 16 * ci4) vi[u] = *reinterpret_cast<const float4*>(in + (int64_t)rr * Cin + 4 * k4);
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int e = threadIdx.x + 256 * u;  // < 8 Cin <= 2048
-      if (e < 8 * Cin) {
-        if (!q.transW) {
-          const int k = e >> 3, c4 = e & 7;  // W is [Cin][Cout]
-          vw[u] = j0 + 4 * c4 < Cout
-                      ? *reinterpret_cast<const float4*>(W + (int64_t)k * Cout + j0 + 4 * c4)
-                      : float4{0.f, 0.f, 0.f, 0.f};
-        } else {
-          const int c = e & 31, k4 = e >> 5;  // W is [Cout][Cin]
-          vw[u] = j0 + c < Cout
-                      ? *reinterpret_cast<const float4*>(W + (int64_t)(j0 + c) * Cin + 4 * k4)
-                      : float4{0.f, 0.f, 0.f, 0.f};
-        }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = threadIdx.x + 256 * u;
-      if (e < 16 * ci4) {
-        const int r = e & 15, k4 = e >> 4;
-        const float4 v = r0 + r < M ? vi[u] : float4{0.f, 0.f, 0.f, 0.f};
-        in_s[(4 * k4 + 0) * 16 + r] = v.x;
-        in_s[(4 * k4 + 1) * 16 + r] = v.y;
-        in_s[(4 * k4 + 2) * 16 + r] = v.z;
-        in_s[(4 * k4 + 3) * 16 + r] = v.w;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int e = threadIdx.x + 256 * u;
-      if (e < 8 * Cin) {
-        if (!q.transW) {
-          const int k = e >> 3, c4 = e & 7;
-          *reinterpret_cast<float4*>(w_s + k * 32 + 4 * c4) = vw[u];
-        } else {
-          const int c = e & 31, k4 = e >> 5;
-          w_s[(4 * k4 + 0) * 32 + c] = vw[u].x;
-          w_s[(4 * k4 + 1) * 32 + c] = vw[u].y;
-          w_s[(4 * k4 + 2) * 32 + c] = vw[u].z;
-          w_s[(4 * k4 + 3) * 32 + c] = vw[u].w;
-        }
-      }
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int k = kb; k < kb + kq; ++k) {
-      const float2 iv = *reinterpret_cast<const float2*>(in_s + k * 16 + 2 * rp);
-      const float4 wv = *reinterpret_cast<const float4*>(w_s + k * 32 + 4 * cg);
-      acc[0][0] += iv.x * wv.x; acc[0][1] += iv.x * wv.y; acc[0][2] += iv.x * wv.z; acc[0][3] += iv.x * wv.w;
-      acc[1][0] += iv.y * wv.x; acc[1][1] += iv.y * wv.y; acc[1][2] += iv.y * wv.z; acc[1][3] += iv.y * wv.w;
-    }
-    __syncthreads();  // the next product restages in_s / w_s
-  }
-  // K quarters -> one output, added in wave order
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-    *reinterpret_cast<float4*>(red + (wave * 16 + 2 * rp + i) * 32 + 4 * cg) =
-        float4{acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
-  __syncthreads();
-  const int po = q.sum ? 0 : blockIdx.z;
-  for (int e = threadIdx.x; e < 16 * 32; e += 256) {
-    const int r = e >> 5, c = e & 31;
-    if (r0 + r >= M || j0 + c >= Cout) continue;
-    const float v = ((red[e] + red[512 + e]) + red[1024 + e]) + red[1536 + e];
-    const float bj = q.b[po] ? q.b[po][j0 + c] : 0.f;
-    q.out[po][(int64_t)(r0 + r) * Cout + j0 + c] = v + bj;
-  }
-}
-
-hipError_t launch_proj(const Proj& q, hipStream_t st) {
-  // (Cin <= 256: the staging loads of k_proj cover 4 Cin and 8 Cin float4)
-  if (q.n < 1 || q.n > 3 || q.M < 1 || q.M > 64 || q.Cin < 16 || q.Cin % 16 || q.Cin > 256 ||
-      q.Cout < 16 || q.Cout % 16)
-    return hipErrorInvalidValue;
-  for (int p = 0; p < q.n; ++p)
-    if (!q.in[p] || !q.W[p] || (!q.sum && !q.out[p])) return hipErrorInvalidValue;
-  if (q.sum && !q.out[0]) return hipErrorInvalidValue;
-  const size_t lds = ((size_t)q.Cin * 48 + 4 * 16 * 32) * sizeof(float);
-  if (lds > 160 * 1024) return hipErrorInvalidConfiguration;
-  dim3 grid((q.Cout + 31) / 32, (q.M + 15) / 16, q.sum ? 1 : q.n);
-  hipLaunchKernelGGL(k_proj, grid, dim3(256), lds, st, q);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// Attention core, one block per head.  Q_h, K_h, V_h (and dO_h) are staged
-// in LDS when they fit (always for D <= 64); otherwise read from global.
-// The row softmax (and the backward's row sums) use G = 256 / Mp lanes per
-// row (Mp = M rounded up to a power of two), reduced with lane shuffles.
-// ---------------------------------------------------------------------------
-static size_t core_lds(int M, int D, int nmat) {
-  return ((size_t)nmat * M * (D + 1) + 2 * (size_t)M * (M + 1)) * sizeof(float);
-}
-
-// Stage nmat [M][D] blocks (columns [off, off + D) of [M][C] matrices) into
-// LDS rows of stride DS: per round, each thread loads 4 elements of every
-// matrix (one index division shared by the matrices) before storing them.
-template <int NMAT>
-__device__ __forceinline__ void stage_heads(const float* const (&src)[NMAT], float* const (&dst)[NMAT],
-                                            int M, int D, int C, int off, int DS) {
-  const int per = M * D;
-  for (int base = threadIdx.x; base < per; base += 4 * kThreads) {
-    float v[NMAT][4];
-    int ri[4], di[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = base + u * kThreads;
-      const int x = e < per ? e : per - 1;
-      ri[u] = x / D;
-      di[u] = x - ri[u] * D;
-#pragma unroll
-      for (int m = 0; m < NMAT; ++m) v[m][u] = src[m][(int64_t)ri[u] * C + off + di[u]];
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (base + u * kThreads < per)
-#pragma unroll
-        for (int m = 0; m < NMAT; ++m) dst[m][ri[u] * DS + di[u]] = v[m][u];
-  }
-}
-
-__device__ __forceinline__ int row_lanes(int M) {
-  int mp = 1;
-  while (mp < M) mp <<= 1;
-  const int g = 256 / mp;  // a row's lanes stay inside one wave
-  return g < 64 ? g : 64;  // 4 .. 64 (a power of two)
-}
-
-template <typename Op>
-__device__ __forceinline__ float lanes_reduce(float v, int G, Op op) {
-  for (int o = 1; o < G; o <<= 1) v = op(v, __shfl_xor(v, o));
-  return v;
-}
-
-template <bool STAGE>
-__global__ void __launch_bounds__(256) k_attn_core(const float* Q, const float* K, const float* V,
-                                                   float* P, float* O, int M, int C, int H) {
-  extern __shared__ __attribute__((aligned(16))) float sm[];
-  const int h = blockIdx.x, D = C / H, off = h * D, DS = D + 1, MS = M + 1;
-  float* sp = sm;                            // [M][M+1]
-  float* qs = sm + 2 * M * MS;               // [M][D+1] x 3
-  float* ks = qs + M * DS;
-  float* vs = ks + M * DS;
-  if (STAGE) {
-    const float* src[3] = {Q, K, V};
-    float* const dst[3] = {qs, ks, vs};
-    stage_heads<3>(src, dst, M, D, C, off, DS);
-    __syncthreads();
-  }
-  auto q_ = [&](int r, int d) { return STAGE ? qs[r * DS + d] : Q[r * C + off + d]; };
-  auto k_ = [&](int r, int d) { return STAGE ? ks[r * DS + d] : K[r * C + off + d]; };
-  auto v_ = [&](int r, int d) { return STAGE ? vs[r * DS + d] : V[r * C + off + d]; };
-  const float scale = 1.0f / sqrtf((float)D);
-  for (int e = threadIdx.x; e < M * M; e += blockDim.x) {
-    const int r = e / M, c = e - r * M;
-    float s = 0.f;
-    for (int d = 0; d < D; ++d) s += q_(r, d) * k_(c, d);
-    sp[r * MS + c] = s * scale;
-  }
-  __syncthreads();
-  {
-    // row r = tid / G, its columns c = lane-in-row + G j
-    const int G = row_lanes(M), r = threadIdx.x / G, li = threadIdx.x - r * G;
-    float mx = -INFINITY;
-    if (r < M)
-      for (int c = li; c < M; c += G) mx = fmaxf(mx, sp[r * MS + c]);
-    mx = lanes_reduce(mx, G, [](float a, float b) { return fmaxf(a, b); });
-    float sum = 0.f;
-    if (r < M)
-      for (int c = li; c < M; c += G) {
-        const float e = expf(sp[r * MS + c] - mx);
-        sp[r * MS + c] = e;
-        sum += e;
-      }
-    sum = lanes_reduce(sum, G, [](float a, float b) { return a + b; });
-    const float inv = 1.0f / sum;
-    if (r < M)
-      for (int c = li; c < M; c += G) sp[r * MS + c] *= inv;
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < M * M; e += blockDim.x) {
-    const int r = e / M, c = e - r * M;
-    P[(int64_t)h * M * M + e] = sp[r * MS + c];
-  }
-  for (int e = threadIdx.x; e < M * D; e += blockDim.x) {
-    const int r = e / D, d = e - r * D;
-    float s = 0.f;
-    for (int c = 0; c < M; ++c) s += sp[r * MS + c] * v_(c, d);
-    O[r * C + off + d] = s;
-  }
-}
-
-hipError_t launch_attn_core(const float* Q, const float* K, const float* V, float* P, float* O,
-                            int M, int C, int H, hipStream_t st) {
-  if (!Q || !K || !V || !P || !O || M < 1 || M > 64 || H < 1 || C % H) return hipErrorInvalidValue;
-  const int D = C / H;
-  const size_t lds = core_lds(M, D, 3);
-  if (lds <= 150 * 1024)
-    hipLaunchKernelGGL(k_attn_core<true>, dim3(H), dim3(256), lds, st, Q, K, V, P, O, M, C, H);
-  else
-    hipLaunchKernelGGL(k_attn_core<false>, dim3(H), dim3(256), core_lds(M, 0, 0), st, Q, K, V, P,
-                       O, M, C, H);
-  return hipGetLastError();
-}
-
-template <bool STAGE>
-__global__ void __launch_bounds__(256) k_attn_core_bwd(const float* Q, const float* K,
-                                                       const float* V, const float* P,
-                                                       const float* dO, float* dQ, float* dK,
-                                                       float* dV, int M, int C, int H) {
-  extern __shared__ __attribute__((aligned(16))) float sm[];
-  const int h = blockIdx.x, D = C / H, off = h * D, DS = D + 1, MS = M + 1;
-  float* sp = sm;                 // P   [M][M+1]
-  float* se = sp + M * MS;        // dE  [M][M+1]
-  float* qs = se + M * MS;        // [M][D+1] x 4
-  float* ks = qs + M * DS;
-  float* vs = ks + M * DS;
-  float* os = vs + M * DS;
-  const float* Ph = P + (int64_t)h * M * M;
-  staged<8>(M * M, [&](int e) { return Ph[e]; },
-            [&](int e, float v) { const int r = e / M; sp[r * MS + (e - r * M)] = v; });
-  if (STAGE) {
-    const float* src[4] = {Q, K, V, dO};
-    float* const dst[4] = {qs, ks, vs, os};
-    stage_heads<4>(src, dst, M, D, C, off, DS);
-  }
-  __syncthreads();
-  auto q_ = [&](int r, int d) { return STAGE ? qs[r * DS + d] : Q[r * C + off + d]; };
-  auto k_ = [&](int r, int d) { return STAGE ? ks[r * DS + d] : K[r * C + off + d]; };
-  auto v_ = [&](int r, int d) { return STAGE ? vs[r * DS + d] : V[r * C + off + d]; };
-  auto o_ = [&](int r, int d) { return STAGE ? os[r * DS + d] : dO[r * C + off + d]; };
-  const float scale = 1.0f / sqrtf((float)D);
-  // dP = dO_h V_h^T
-  for (int e = threadIdx.x; e < M * M; e += blockDim.x) {
-    const int r = e / M, c = e - r * M;
-    float s = 0.f;
-    for (int d = 0; d < D; ++d) s += o_(r, d) * v_(c, d);
-    se[r * MS + c] = s;
-  }
-  __syncthreads();
-  // dE = P o (dP - rowsum(dP o P))
-  {
-    const int G = row_lanes(M), r = threadIdx.x / G, li = threadIdx.x - r * G;
-    float rs = 0.f;
-    if (r < M)
-      for (int c = li; c < M; c += G) rs += se[r * MS + c] * sp[r * MS + c];
-    rs = lanes_reduce(rs, G, [](float a, float b) { return a + b; });
-    if (r < M)
-      for (int c = li; c < M; c += G) se[r * MS + c] = sp[r * MS + c] * (se[r * MS + c] - rs);
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < M * D; e += blockDim.x) {
-    const int r = e / D, d = e - r * D;
-    float sv = 0.f, sq = 0.f, sk = 0.f;
-    for (int c = 0; c < M; ++c) {
-      sv += sp[c * MS + r] * o_(c, d);
-      sq += se[r * MS + c] * k_(c, d);
-      sk += se[c * MS + r] * q_(c, d);
-    }
-    dV[r * C + off + d] = sv;
-    dQ[r * C + off + d] = scale * sq;
-    dK[r * C + off + d] = scale * sk;
-  }
-}
-
-hipError_t launch_attn_core_bwd(const float* Q, const float* K, const float* V,
-                                const float* P, const float* dO, float* dQ, float* dK,
-                                float* dV, int M, int C, int H, hipStream_t st) {
-  if (!Q || !K || !V || !P || !dO || !dQ || !dK || !dV || M < 1 || M > 64 || H < 1 || C % H)
-    return hipErrorInvalidValue;
-  const int D = C / H;
-  const size_t lds = core_lds(M, D, 4);
-  if (lds <= 150 * 1024)
-    hipLaunchKernelGGL(k_attn_core_bwd<true>, dim3(H), dim3(256), lds, st, Q, K, V, P, dO, dQ,
-                       dK, dV, M, C, H);
-  else
-    hipLaunchKernelGGL(k_attn_core_bwd<false>, dim3(H), dim3(256), core_lds(M, 0, 0), st, Q, K,
-                       V, P, dO, dQ, dK, dV, M, C, H);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// Fused per-head kernels.  One block of kHeadThreads per head.  Every
-// contraction runs on v_mfma_f32_16x16x4f32 over 16 x 16 tiles.  Operand
-// runs of 4 consecutive k are read as float4 (lane group g, step q:
-// k = 16q + 4g .. +3, the same k on both sides, so the pairing is exact).
-//   Projections: tiles (matrix m in {Q, K, V}, row tile mt, column tile nt),
-//     wave w owning tiles w, w + kHeadWaves, ...; the contraction over C runs
-//     in K chunks of KC: the chunk of S (rows >= M zero) and of the head's
-//     columns of W_m, transposed (columns >= D zero), are staged in LDS with
-//     one round of loads.  Q_h, K_h, V_h are then kept in LDS as zero-padded
-//     [M16][D16 + 4] tiles (the core buffers alias the chunk buffers).
-//   Core: wave mt owns query rows [16mt, 16mt + 16).  Its scores are formed
-//     transposed (K_h Q_h^T), so that lane (r, g) holds row 16mt + r at
-//     columns 16ct + 4g + i: the row softmax reduces in-lane and across the
-//     four lane groups, and P is already the A operand of P V_h.
-// ---------------------------------------------------------------------------
-constexpr int kHeadThreads = 512;
-constexpr int kHeadWaves = kHeadThreads / 64;
-constexpr int kHeadTPW = 4;        // projection tiles per wave (at most)
-constexpr int kHeadDO = 8;         // padded dO_h elements per thread (at most)
 
 __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
-// acc += sum_i a[i] b[i] over the 4 k of a float4 run
-__device__ __forceinline__ f32x4 mfma4x4(const f32x4& a, const f32x4& b, f32x4 c) {
-  c = mfma4(a[0], b[0], c);
-  c = mfma4(a[1], b[1], c);
-  c = mfma4(a[2], b[2], c);
-  return mfma4(a[3], b[3], c);
-}
 
-// A kernel-argument pointer as an opaque uniform register value: choosing
-// among such values per lane stays a register select (an indexed read of the
-// argument array would copy the arguments to scratch memory).
-template <typename P> __device__ __forceinline__ P in_sreg(P p) {
-  asm volatile("" : "+s"(p));
-  return p;
-}
-struct Ptr3 {
-  const float *p0, *p1, *p2;
-  __device__ __forceinline__ const float* operator()(int m) const {
-    return m == 0 ? p0 : m == 1 ? p1 : p2;
-  }
-};
-__device__ __forceinline__ Ptr3 ptr3(const float* const (&v)[3]) {
-  return {in_sreg(v[0]), in_sreg(v[1]), in_sreg(v[2])};
-}
+// ---------------------------------------------------------------------------
+// k_proj: one 16 x 16 tile of product blockIdx.z per block.  The K = Cin steps
+// of 4 (lane group g: k = 4 s + g, so that a lane row's four groups read 16
+// contiguous bytes) split over the four waves, their sums added in wave order.
+// ---------------------------------------------------------------------------
+constexpr int kProjSteps = 16;  // K4 steps per wave (Cin <= 256)
 
-struct HeadTile { int m, mt, nt; };
-__device__ __forceinline__ HeadTile head_tile(const HeadGeo& G, int t) {
-  const int m = t / (G.MT * G.NT), rem = t - m * G.MT * G.NT;
-  return {m, rem / G.NT, rem - (rem / G.NT) * G.NT};
-}
-
-// Projection tiles of the calling wave (tile j = wave + kHeadWaves j) in
-// acc, with their biases in bias (lane (r, g): column 16 nt + r).
-__device__ __forceinline__ void head_project(const HeadArgs& a, float* sm, f32x4 (&acc)[kHeadTPW],
-                                             float (&bias)[kHeadTPW]) {
-  const HeadGeo& G = a.geo;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  const int tid = threadIdx.x, off = blockIdx.x * G.D;
-  float* s_ch = sm;                    // [M16][SR]
-  float* w_ch = sm + G.M16 * G.SR;     // [3 D16][SR]
-  const Ptr3 b = ptr3(a.b);
-  int sa[kHeadTPW], sb[kHeadTPW];
-#pragma unroll
-  for (int j = 0; j < kHeadTPW; ++j) {
-    acc[j] = zero4();
-    const int t = wave + kHeadWaves * j;
-    const HeadTile h = head_tile(G, t < G.T ? t : 0);
-    sa[j] = (16 * h.mt + r) * G.SR + 4 * g;
-    sb[j] = (h.m * G.D16 + 16 * h.nt + r) * G.SR + 4 * g;
-    const int col = 16 * h.nt + r;
-    const float* bm = b(h.m);
-    bias[j] = (t < G.T && bm != nullptr && col < G.D) ? bm[off + col] : 0.f;
-  }
-  // KC and D16 are powers of two (C is, and D divides it): shifts, not
-  // divisions.  Per round each thread has 4 S and 4 x 3 W float4 loads in
-  // flight before its LDS stores.
-  const int KC4 = G.KC / 4, D4 = G.D16 / 4;
-  const int lKC4 = __builtin_ctz(KC4), lD4 = __builtin_ctz(D4);
-  const int nS4 = G.M16 * KC4, nW4 = G.KC * D4;
-  const int nmax = nS4 > nW4 ? nS4 : nW4;
-  for (int k0 = 0; k0 < G.C; k0 += G.KC) {
-    for (int base = tid; base < nmax; base += 4 * kHeadThreads) {
-      float4 vs[4], vw[3][4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int e = base + u * kHeadThreads;
-        const int es = e < nS4 ? e : nS4 - 1;
-        const int row = es >> lKC4, c4 = es & (KC4 - 1);
-        const int rr = row < G.M ? row : G.M - 1;
-        vs[u] = *reinterpret_cast<const float4*>(a.S + rr * G.C + k0 + 4 * c4);
-        const int ew = e < nW4 ? e : nW4 - 1;
-        const int k = ew >> lD4, d4 = ew & (D4 - 1);
-        const int dd = 4 * d4 < G.D ? 4 * d4 : 0;
-#pragma unroll
-        for (int m = 0; m < 3; ++m)
-          vw[m][u] = *reinterpret_cast<const float4*>(a.W[m] + (k0 + k) * G.C + off + dd);
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int e = base + u * kHeadThreads;
-        if (e < nS4) {
-          const int row = e >> lKC4, c4 = e & (KC4 - 1);
-          const float4 v = row < G.M ? vs[u] : float4{0.f, 0.f, 0.f, 0.f};
-          *reinterpret_cast<float4*>(s_ch + row * G.SR + 4 * c4) = v;
-        }
-        if (e < nW4) {
-          const int k = e >> lD4, d4 = e & (D4 - 1);
-          const bool valid = 4 * d4 < G.D;
-#pragma unroll
-          for (int m = 0; m < 3; ++m) {
-            const float4 v = valid ? vw[m][u] : float4{0.f, 0.f, 0.f, 0.f};
-            float* d = w_ch + (m * G.D16 + 4 * d4) * G.SR + k;
-            d[0] = v.x;
-            d[G.SR] = v.y;
-            d[2 * G.SR] = v.z;
-            d[3 * G.SR] = v.w;
-          }
-        }
-      }
-    }
-    __syncthreads();
-    // two K steps per round: the reads of both are issued before the MFMAs
-    for (int q = 0; q < G.KC / 16; q += 2) {
-      f32x4 x0[kHeadTPW], w0[kHeadTPW], x1[kHeadTPW], w1[kHeadTPW];
-#pragma unroll
-      for (int j = 0; j < kHeadTPW; ++j) {
-        if (wave + kHeadWaves * j < G.T) {
-          x0[j] = *reinterpret_cast<const f32x4*>(s_ch + sa[j] + 16 * q);
-          w0[j] = *reinterpret_cast<const f32x4*>(w_ch + sb[j] + 16 * q);
-          x1[j] = *reinterpret_cast<const f32x4*>(s_ch + sa[j] + 16 * q + 16);
-          w1[j] = *reinterpret_cast<const f32x4*>(w_ch + sb[j] + 16 * q + 16);
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < kHeadTPW; ++j)
-        if (wave + kHeadWaves * j < G.T) acc[j] = mfma4x4(x0[j], w0[j], acc[j]);
-#pragma unroll
-      for (int j = 0; j < kHeadTPW; ++j)
-        if (wave + kHeadWaves * j < G.T) acc[j] = mfma4x4(x1[j], w1[j], acc[j]);
-    }
-    __syncthreads();  // the chunk buffers are restaged, or become the core's
-  }
-}
-
-// Projection tiles -> zero-padded Q_h, K_h, V_h tiles ([M16][QS] each at qkv).
-__device__ __forceinline__ void head_store_qkv(const HeadGeo& G, const f32x4 (&acc)[kHeadTPW],
-                                               const float (&bias)[kHeadTPW], float* qkv, int QS) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-#pragma unroll
-  for (int j = 0; j < kHeadTPW; ++j) {
-    const int t = wave + kHeadWaves * j;
-    if (t >= G.T) continue;
-    const HeadTile h = head_tile(G, t);
-    const int col = 16 * h.nt + r;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = 16 * h.mt + 4 * g + i;
-      qkv[(h.m * G.M16 + row) * QS + col] = (row < G.M && col < G.D) ? acc[j][i] + bias[j] : 0.f;
-    }
-  }
-}
-
-// Rows [16mt, 16mt + 16) of X Y^T, transposed: lane (r, g) of tile ct holds
-// (X Y^T)[16mt + r][16ct + 4g + i] (X, Y: [M16][QS] tiles, K = D16).
-__device__ __forceinline__ void head_rows_xyt(const float* X, const float* Y, int mt, int MT,
-                                              int D16, int QS, f32x4 (&t)[4]) {
+__global__ void __launch_bounds__(256) k_proj(Proj q) {
+  __shared__ f32x4 part[3][64];
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int p = blockIdx.z, M = q.M, Cin = q.Cin, Cout = q.Cout;
+  // (by constant index: a run-time index would copy the arguments to scratch)
+  auto pick = [p](auto const (&v)[kProjMax]) {
+    return p == 0 ? v[0] : p == 1 ? v[1] : p == 2 ? v[2] : p == 3 ? v[3] : v[4];
+  };
+  const float* in = pick(q.in);
+  const float* W = pick(q.W);
+  const float* b = pick(q.b);
+  const bool tr = pick(q.transW);
+  const int i0 = 16 * blockIdx.y, j0 = 16 * blockIdx.x;
+  const int row = i0 + r < M ? i0 + r : M - 1, col = j0 + r;  // (Cout a multiple of 16)
+  const int n = Cin / 16, k0 = 4 * n * wave + g;              // steps per wave, its first k
+  const int64_t wk = tr ? 1 : Cout;
+  const float* ip = in + (int64_t)row * Cin + k0;
+  const float* wp = W + (tr ? (int64_t)col * Cin : col) + k0 * wk;
+  float x[kProjSteps], w[kProjSteps], c[kProjSteps];
+  const bool center = pick(q.center);
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct) {
-    t[ct] = zero4();
-    if (ct < MT)
-      for (int q = 0; q < D16 / 16; ++q) {
-        const f32x4 y = *reinterpret_cast<const f32x4*>(Y + (16 * ct + r) * QS + 16 * q + 4 * g);
-        const f32x4 x = *reinterpret_cast<const f32x4*>(X + (16 * mt + r) * QS + 16 * q + 4 * g);
-        t[ct] = mfma4x4(y, x, t[ct]);
-      }
+  for (int s = 0; s < kProjSteps; ++s) {
+    if (s < n) {
+      x[s] = ip[4 * s];
+      w[s] = wp[4 * s * wk];
+      c[s] = center ? in[k0 + 4 * s] : 0.f;
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < kProjSteps; ++s)
+    if (s < n) x[s] -= c[s];
+  f32x4 acc = zero4();
+#pragma unroll
+  for (int s = 0; s < kProjSteps; ++s)
+    if (s < n) acc = mfma4(x[s], w[s], acc);
+  if (wave > 0) part[wave - 1][lane] = acc;
+  __syncthreads();
+  if (wave > 0) return;
+  acc = ((acc + part[0][lane]) + part[1][lane]) + part[2][lane];
+  const float bj = b ? b[col] : 0.f;
+  float* out = pick(q.out);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int orow = i0 + 4 * g + i;
+    if (orow < M) out[(int64_t)orow * Cout + col] = acc[i] + bj;
   }
 }
 
-// Row softmax of the transposed score rows (columns >= M masked): P in place.
-__device__ __forceinline__ void head_row_softmax(f32x4 (&p)[4], int MT, int M, float scale) {
-  const int lane = threadIdx.x & 63, g = lane >> 4;
+hipError_t launch_proj(const Proj& q, hipStream_t st) {
+  // (Cin <= 256: kProjSteps K4 steps per wave)
+  if (q.n < 1 || q.n > kProjMax || q.M < 1 || q.M > 64 || q.Cin < 16 || q.Cin % 16 || q.Cin > 256 ||
+      q.Cout < 16 || q.Cout % 16)
+    return hipErrorInvalidValue;
+  for (int p = 0; p < q.n; ++p)
+    if (!q.in[p] || !q.W[p] || !q.out[p]) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_proj, dim3(q.Cout / 16, (q.M + 15) / 16, q.n), dim3(256), 0, st, q);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// Attention cores.  Scores are formed transposed, X Y^T with the keys as rows:
+// lane (r, g) of tile t, element e, holds (query 16 qt + r, key 16 t + 4 g + e),
+// so a query's softmax reduces in the lane and over the four lane groups, and
+// the probabilities are already the B operand of (P V)^T = V^T P^T (step (t,
+// e): key 16 t + 4 g + e).  Rows past M re-read row M - 1; their results are
+// masked (keys) or not stored (queries).
+// ---------------------------------------------------------------------------
+// A head's matrix: element (row, d), in global memory or staged in LDS.
+struct HeadMat {
+  const float* p;
+  int ld;
+  __device__ __forceinline__ float operator()(int row, int d) const { return p[row * ld + d]; }
+};
+
+template <int MT>
+__device__ __forceinline__ void core_scores(const HeadMat& X, const HeadMat& Y, int qt, int M,
+                                            int D, f32x4 (&p)[MT]) {
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int qi = 16 * qt + r < M ? 16 * qt + r : M - 1;
+  int yj[MT];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    yj[t] = 16 * t + r < M ? 16 * t + r : M - 1;
+    p[t] = zero4();
+  }
+  for (int d0 = 0; d0 < D; d0 += 32) {
+    float x[8], y[MT][8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const int d = d0 + 4 * s + g;
+      const bool in = d < D;
+      const int dd = in ? d : 0;
+      x[s] = X(qi, dd);
+      if (!in) x[s] = 0.f;
+#pragma unroll
+      for (int t = 0; t < MT; ++t) {
+        y[t][s] = Y(yj[t], dd);
+        if (!in) y[t][s] = 0.f;
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+      if (d0 + 4 * s < D)
+#pragma unroll
+        for (int t = 0; t < MT; ++t) p[t] = mfma4(y[t][s], x[s], p[t]);
+  }
+}
+
+template <int MT>
+__device__ __forceinline__ void core_softmax(f32x4 (&p)[MT], int M, float scale) {
+  const int g = (threadIdx.x & 63) >> 4;
   float mx = -INFINITY;
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct)
-    if (ct < MT)
+  for (int t = 0; t < MT; ++t)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const bool v = 16 * ct + 4 * g + i < M;
-        p[ct][i] = v ? p[ct][i] * scale : -INFINITY;
-        mx = fmaxf(mx, p[ct][i]);
-      }
+    for (int e = 0; e < 4; ++e) {
+      p[t][e] = 16 * t + 4 * g + e < M ? p[t][e] * scale : -INFINITY;
+      mx = fmaxf(mx, p[t][e]);
+    }
   mx = fmaxf(mx, __shfl_xor(mx, 16));
   mx = fmaxf(mx, __shfl_xor(mx, 32));
   float sum = 0.f;
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct)
-    if (ct < MT)
+  for (int t = 0; t < MT; ++t)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        p[ct][i] = expf(p[ct][i] - mx);
-        sum += p[ct][i];
-      }
+    for (int e = 0; e < 4; ++e) {
+      p[t][e] = expf(p[t][e] - mx);
+      sum += p[t][e];
+    }
   sum += __shfl_xor(sum, 16);
   sum += __shfl_xor(sum, 32);
   const float inv = 1.0f / sum;
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct)
-    if (ct < MT) p[ct] *= inv;
+  for (int t = 0; t < MT; ++t) p[t] *= inv;
 }
 
-// Tile (mt, dt) of A V: A in the transposed-row layout (tiles ct), V a
-// [M16][QS] tile in LDS.  Result lane (r, g): row 16mt + 4g + i, column
-// 16dt + r.
-__device__ __forceinline__ f32x4 head_rows_times(const f32x4 (&A)[4], const float* V, int dt, int MT,
-                                                 int QS) {
+// Channels d0 + r of the keys' rows, as the A operand of core_times.
+template <int MT>
+__device__ __forceinline__ void core_rows(float (&z)[MT][4], const HeadMat& Z, int d0, int M,
+                                          int D) {
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  f32x4 o = zero4();
+  const int d = d0 + r < D ? d0 + r : D - 1;  // (channels past D are not stored)
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct)
-    if (ct < MT)
+  for (int t = 0; t < MT; ++t)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) o = mfma4(A[ct][i], V[(16 * ct + 4 * g + i) * QS + 16 * dt + r], o);
-  return o;
-}
-
-// Global store of a result tile (lane (r, g): row 16 rt + 4g + i, column
-// 16 ct + r of the head's [M, D] block of dst).
-__device__ __forceinline__ void head_put(float* dst, const f32x4& v, int rt, int ct, int M, int D,
-                                         int C, int off, float scale) {
-  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  const int col = 16 * ct + r;
-  if (col >= D) return;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = 16 * rt + 4 * g + i;
-    if (row < M) dst[row * C + off + col] = scale * v[i];
-  }
-}
-
-__global__ void __launch_bounds__(kHeadThreads) k_head_fwd(HeadArgs a) {
-  extern __shared__ __attribute__((aligned(16))) float sm[];
-  const HeadGeo& G = a.geo;
-  const int QS = G.D16 + 4, off = blockIdx.x * G.D, wave = threadIdx.x >> 6;
-  f32x4 acc[kHeadTPW];
-  float bias[kHeadTPW];
-  head_project(a, sm, acc, bias);
-  float* qs = sm;
-  float* ks = qs + G.M16 * QS;
-  float* vs = ks + G.M16 * QS;
-  head_store_qkv(G, acc, bias, qs, QS);
-  __syncthreads();
-  if (wave < G.MT) {
-    f32x4 p[4];
-    head_rows_xyt(qs, ks, wave, G.MT, G.D16, QS, p);
-    head_row_softmax(p, G.MT, G.M, 1.0f / sqrtf((float)G.D));
-    for (int dt = 0; dt < G.NT; ++dt)
-      head_put(a.O, head_rows_times(p, vs, dt, G.MT, QS), wave, dt, G.M, G.D, G.C, off, 1.f);
-  }
-}
-
-__global__ void __launch_bounds__(kHeadThreads) k_head_bwd(HeadArgs a) {
-  extern __shared__ __attribute__((aligned(16))) float sm[];
-  const HeadGeo& G = a.geo;
-  const int QS = G.D16 + 4, PS = G.M16 + 4, off = blockIdx.x * G.D, wave = threadIdx.x >> 6;
-  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  const int C = G.C, M = G.M, D = G.D, MT = G.MT, NT = G.NT;
-  // padded dO_h in registers first: its loads overlap the projections
-  const int lD16 = __builtin_ctz(G.D16), nDO = G.M16 * G.D16;
-  float dov[kHeadDO];
-#pragma unroll
-  for (int u = 0; u < kHeadDO; ++u) {
-    const int e = threadIdx.x + u * kHeadThreads;
-    const int x = e < nDO ? e : nDO - 1;
-    const int row = x >> lD16, col = x & (G.D16 - 1);
-    const int rr = row < M ? row : M - 1, cc = col < D ? col : D - 1;
-    dov[u] = a.dO[rr * C + off + cc];
-  }
-  f32x4 acc[kHeadTPW];
-  float bias[kHeadTPW];
-  head_project(a, sm, acc, bias);
-  float* qs = sm;
-  float* ks = qs + G.M16 * QS;
-  float* vs = ks + G.M16 * QS;
-  float* os = vs + G.M16 * QS;  // dO_h
-  float* ps = os + G.M16 * QS;  // P  [M16][PS]
-  float* es = ps + G.M16 * PS;  // dE [M16][PS]
-  head_store_qkv(G, acc, bias, qs, QS);
-#pragma unroll
-  for (int u = 0; u < kHeadDO; ++u) {
-    const int e = threadIdx.x + u * kHeadThreads;
-    if (e < nDO) {
-      const int row = e >> lD16, col = e & (G.D16 - 1);
-      os[row * QS + col] = (row < M && col < D) ? dov[u] : 0.f;
+    for (int e = 0; e < 4; ++e) {
+      const int j = 16 * t + 4 * g + e;
+      z[t][e] = Z(j < M ? j : M - 1, d);
+      if (j >= M) z[t][e] = 0.f;
     }
+}
+// dst (row stride C) rows 16 qt .., channels d0 .. d0 + 15 of scale A Z (A in
+// the transposed layout above), in two chains of MFMAs.
+template <int MT>
+__device__ __forceinline__ void core_times(const f32x4 (&A)[MT], const float (&z)[MT][4],
+                                           float* dst, int qt, int d0, int M, int D, int C,
+                                           float scale) {
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int qi = 16 * qt + r;
+  f32x4 o[2] = {zero4(), zero4()};
+#pragma unroll
+  for (int t = 0; t < MT; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e & 1] = mfma4(z[t][e], A[t][e], o[e & 1]);
+  o[0] += o[1];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int od = d0 + 4 * g + e;
+    if (od < D && qi < M) dst[(int64_t)qi * C + od] = scale * o[0][e];
   }
-  __syncthreads();
+}
+
+template <int MT>
+__global__ void __launch_bounds__(64) k_core(CoreArgs a) {
+  const int M = a.M, C = a.C, D = C / a.H, off = blockIdx.x * D, qt = blockIdx.y;
+  const HeadMat V{a.V + off, C};
+  float z[MT][4];
+  core_rows<MT>(z, V, 0, M, D);  // (requested with Q and K)
+  f32x4 p[MT];
+  core_scores<MT>({a.Q + off, C}, {a.K + off, C}, qt, M, D, p);
+  core_softmax<MT>(p, M, 1.0f / sqrtf((float)D));
+  for (int d0 = 0; d0 < D; d0 += 16) {
+    if (d0 > 0) core_rows<MT>(z, V, d0, M, D);
+    core_times<MT>(p, z, a.O + off, qt, d0, M, D, C, 1.f);
+  }
+}
+
+// One block of eight waves per head.  The head's Q, K, V, dO are staged in LDS
+// in one round of loads (STAGE; heads too wide for it read global memory).
+// Waves qt < MT: P, dP = dO V^T and dE = P o (dP - rowsum(dP o P)) of 16 query
+// rows, to LDS; then all waves form the tiles of dQ = scale dE K, dK = scale
+// dE^T Q, dV = P^T dO and, where wanted, O = P Vf.
+constexpr int kCoreBwdWaves = 8;
+__host__ __device__ constexpr int core_ld(int D) { return D + 4; }  // staged row stride
+
+template <int MT, bool STAGE>
+__global__ void __launch_bounds__(64 * kCoreBwdWaves) k_core_bwd(CoreArgs a) {
+  constexpr int M16 = 16 * MT, PS = M16 + 4, TH = 64 * kCoreBwdWaves;
+  extern __shared__ __attribute__((aligned(16))) float sm[];
+  float* ps = sm;               // P  [query][key]
+  float* es = sm + M16 * PS;    // dE [query][key]
+  float* st = sm + 2 * M16 * PS;
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int M = a.M, C = a.C, D = C / a.H, off = blockIdx.x * D, NT = (D + 15) / 16;
   const float scale = 1.0f / sqrtf((float)D);
+  const int ld = STAGE ? core_ld(D) : C;
+  const HeadMat Q{STAGE ? st : a.Q + off, ld}, K{STAGE ? st + M * ld : a.K + off, ld},
+      V{STAGE ? st + 2 * M * ld : a.V + off, ld}, dO{STAGE ? st + 3 * M * ld : a.dO + off, ld};
+  if constexpr (STAGE) {
+    const int n = M * D;
+    for (int b = threadIdx.x; b < n; b += 4 * TH) {
+      float v[4][4];
+      int o[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int e = b + u * TH < n ? b + u * TH : n - 1;
+        const int row = e / D, d = e - row * D, x = row * C + off + d;
+        o[u] = row * ld + d;
+        v[0][u] = a.Q[x];
+        v[1][u] = a.K[x];
+        v[2][u] = a.V[x];
+        v[3][u] = a.dO[x];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)  // (past the end: the last element again)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) st[m * M * ld + o[u]] = v[m][u];
+    }
+    __syncthreads();
+  }
   if (wave < MT) {
-    // P, dP = dO_h V_h^T and dE = P o (dP - rowsum(dP o P)) for the wave's
-    // rows; then dQ_h = scale dE K_h (and O_h = P V_h when wanted)
-    f32x4 p[4], e[4];
-    head_rows_xyt(qs, ks, wave, MT, G.D16, QS, p);
-    head_row_softmax(p, MT, M, scale);
-    head_rows_xyt(os, vs, wave, MT, G.D16, QS, e);
+    f32x4 p[MT], e[MT];
+    core_scores<MT>(Q, K, wave, M, D, p);
+    core_scores<MT>(dO, V, wave, M, D, e);
+    core_softmax<MT>(p, M, scale);
     float rs = 0.f;
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct)
-      if (ct < MT)
+    for (int t = 0; t < MT; ++t)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) rs += e[ct][i] * p[ct][i];
+      for (int i = 0; i < 4; ++i) {
+        if (16 * t + 4 * g + i >= M) e[t][i] = 0.f;  // (P is 0 there)
+        rs += e[t][i] * p[t][i];
+      }
     rs += __shfl_xor(rs, 16);
     rs += __shfl_xor(rs, 32);
+    const bool qv = 16 * wave + r < M;  // rows past M contribute nothing below
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct)
-      if (ct < MT)
+    for (int t = 0; t < MT; ++t) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          e[ct][i] = p[ct][i] * (e[ct][i] - rs);
-          const int o = (16 * wave + r) * PS + 16 * ct + 4 * g + i;
-          ps[o] = p[ct][i];
-          es[o] = e[ct][i];
-        }
-    for (int dt = 0; dt < NT; ++dt) {
-      head_put(a.dX[0], head_rows_times(e, ks, dt, MT, QS), wave, dt, M, D, C, off, scale);
-      if (a.O) head_put(a.O, head_rows_times(p, vs, dt, MT, QS), wave, dt, M, D, C, off, 1.f);
+      for (int i = 0; i < 4; ++i) e[t][i] = p[t][i] * (e[t][i] - rs);
+      const int o = (16 * wave + r) * PS + 16 * t + 4 * g;
+      *reinterpret_cast<f32x4*>(ps + o) = qv ? p[t] : zero4();
+      *reinterpret_cast<f32x4*>(es + o) = qv ? e[t] : zero4();
     }
   }
   __syncthreads();
-  // dK_h = scale dE^T Q_h and dV_h = P^T dO_h: tiles (which, key tile ct,
-  // column tile dt) over the waves; K = the query rows
-  for (int t = wave; t < 2 * MT * NT; t += kHeadWaves) {
+  // tile (which, row tile ct, channel tile dt); the contraction runs over the
+  // keys (dQ, O: A^T = the row's probabilities) or over the queries (dK, dV)
+  const int tiles = (a.O ? 4 : 3) * MT * NT;
+  for (int t = wave; t < tiles; t += kCoreBwdWaves) {
     const int which = t / (MT * NT), rem = t - which * MT * NT;
     const int ct = rem / NT, dt = rem - ct * NT;
-    const float* Am = which == 0 ? es : ps;
-    const float* Bm = which == 0 ? qs : os;
-    f32x4 o = zero4();
-    for (int q = 0; q < MT; ++q)
+    const float* Am = which == 0 || which == 1 ? es : ps;
+    const bool keys = which == 0 || which == 3;  // contraction over the keys
+    const HeadMat Vf{a.Vf + off, C};  // (global memory: read for O only)
+    const HeadMat Bm = which == 0 ? K : which == 1 ? Q : which == 2 ? dO : Vf;
+    const int d = 16 * dt + r < D ? 16 * dt + r : D - 1;
+    float b[4 * MT], x[4 * MT];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = 16 * q + 4 * g + i;
-        o = mfma4(Am[row * PS + 16 * ct + r], Bm[row * QS + 16 * dt + r], o);
-      }
-    head_put(which == 0 ? a.dX[1] : a.dX[2], o, ct, dt, M, D, C, off, which == 0 ? scale : 1.f);
-  }
-}
-
-// Geometry of the fused head kernels, or false if the head does not fit.
-static bool head_geo(int M, int C, int H, bool bwd, HeadGeo& G) {
-  if (M < 1 || M > 64 || H < 1 || C % H || C < 16 || (C & (C - 1))) return false;
-  G.M = M; G.C = C; G.H = H; G.D = C / H;  // C, and so D, a power of two
-  if (G.D % 4) return false;
-  G.M16 = (M + 15) / 16 * 16;
-  G.D16 = (G.D + 15) / 16 * 16;
-  G.MT = G.M16 / 16; G.NT = G.D16 / 16; G.T = 3 * G.MT * G.NT;
-  if (G.T > kHeadWaves * kHeadTPW) return false;
-  if (bwd && G.M16 * G.D16 > kHeadDO * kHeadThreads) return false;
-  const int QS = G.D16 + 4, PS = G.M16 + 4;
-  const size_t core = ((size_t)(bwd ? 4 : 3) * G.M16 * QS + (bwd ? 2 : 0) * (size_t)G.M16 * PS) * 4;
-  const size_t cap = 150 * 1024;
-  if (core > cap) return false;
-  for (int kc = C; kc >= 32; kc /= 2) {
-    const size_t chunk = ((size_t)G.M16 + 3 * (size_t)G.D16) * (kc + 4) * 4;
-    if (chunk <= cap) {
-      G.KC = kc;
-      G.SR = kc + 4;
-      G.lds = chunk > core ? chunk : core;
-      return true;
+    for (int s = 0; s < 4 * MT; ++s) {
+      const int q = 4 * s + g;
+      b[s] = Bm(q < M ? q : M - 1, d);
+      if (q >= M) b[s] = 0.f;
+      x[s] = keys ? Am[(16 * ct + r) * PS + q] : Am[q * PS + 16 * ct + r];
+    }
+    f32x4 o[2] = {zero4(), zero4()};
+#pragma unroll
+    for (int s = 0; s < 4 * MT; ++s) o[s & 1] = mfma4(x[s], b[s], o[s & 1]);
+    o[0] += o[1];
+    float* dst = (which == 0 ? a.dQ : which == 1 ? a.dK : which == 2 ? a.dV : a.O) + off;
+    const float sc = which < 2 ? scale : 1.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = 16 * ct + 4 * g + i;
+      if (row < M && 16 * dt + r < D) dst[(int64_t)row * C + 16 * dt + r] = sc * o[0][i];
     }
   }
-  return false;
 }
 
-bool head_fits(int M, int C, int H) {
-  HeadGeo G;
-  return head_geo(M, C, H, false, G) && head_geo(M, C, H, true, G);
-}
-
-hipError_t launch_head(HeadArgs a, bool bwd, hipStream_t st) {
-  if (!head_geo(a.geo.M, a.geo.C, a.geo.H, bwd, a.geo)) return hipErrorInvalidConfiguration;
-  if (!a.S || !a.W[0] || !a.W[1] || !a.W[2]) return hipErrorInvalidValue;
-  if (bwd ? (!a.dO || !a.dX[0] || !a.dX[1] || !a.dX[2]) : !a.O) return hipErrorInvalidValue;
-  if (bwd)
-    hipLaunchKernelGGL(k_head_bwd, dim3(a.geo.H), dim3(kHeadThreads), a.geo.lds, st, a);
-  else
-    hipLaunchKernelGGL(k_head_fwd, dim3(a.geo.H), dim3(kHeadThreads), a.geo.lds, st, a);
+hipError_t launch_core(const CoreArgs& a, bool bwd, hipStream_t st) {
+  if (!a.Q || !a.K || !a.V || a.M < 1 || a.M > 64 || a.H < 1 || a.C < 1 || a.C % a.H)
+    return hipErrorInvalidValue;
+  if (bwd ? (!a.dO || !a.dQ || !a.dK || !a.dV) : !a.O) return hipErrorInvalidValue;
+  const int MT = (a.M + 15) / 16, D = a.C / a.H;
+  // LDS of the backward: P, dE, and the head's four matrices where they fit
+  const size_t core = (size_t)2 * 16 * MT * (16 * MT + 4) * sizeof(float);
+  const size_t all = core + (size_t)4 * a.M * core_ld(D) * sizeof(float);
+  const bool stage = all <= (size_t)kLdsBytes;
+  if (bwd && a.O && !a.Vf) return hipErrorInvalidValue;
+#define PA_CORE(T)                                                                             \
+  case T:                                                                                      \
+    if (!bwd)                                                                                  \
+      hipLaunchKernelGGL(k_core<T>, dim3(a.H, T), dim3(64), 0, st, a);                         \
+    else if (stage)                                                                            \
+      hipLaunchKernelGGL((k_core_bwd<T, true>), dim3(a.H), dim3(64 * kCoreBwdWaves), all, st, a);   \
+    else                                                                                       \
+      hipLaunchKernelGGL((k_core_bwd<T, false>), dim3(a.H), dim3(64 * kCoreBwdWaves), core, st, a); \
+    break;
+  switch (MT) { PA_CORE(1) PA_CORE(2) PA_CORE(3) PA_CORE(4) }
+#undef PA_CORE
   return hipGetLastError();
 }
 
@@ -817,6 +413,7 @@ __global__ void __launch_bounds__(256) k_token_grads(GradArgs a) {
   if (!wantW && !wantB) return;
   const float* A = pick(a.A);
   const float* Bm = pick(a.B);
+  const float a0 = pick(a.center) ? A[16 * ct + r] : 0.f;
   const int S4 = (M + 3) / 4;  // K steps: k = 4 s + g
   float av[16], bv[16];
 #pragma unroll
@@ -833,7 +430,7 @@ __global__ void __launch_bounds__(256) k_token_grads(GradArgs a) {
   for (int s = 0; s < 16; ++s) {
     if (s < S4) {
       const bool v = 4 * s + g < M;
-      const float x = v ? av[s] : 0.f, y = v ? bv[s] : 0.f;
+      const float x = v ? av[s] - a0 : 0.f, y = v ? bv[s] : 0.f;
       acc = mfma4(x, y, acc);
       cs += y;
     }

@@ -36,23 +36,24 @@ __device__ __forceinline__ double opnd_ld(const void* p, int64_t off, bool in) {
   return in ? v : 0.0;
 }
 // A wave's operand of the K chunk at k0: lane (r, g) holds index m of step q,
-// k = k0 + 16 g + q (the same k on both operands of the product).
+// k = k0 + 4 q + g (the same k on both operands of the product; a lane row's
+// four groups read 16 or 32 contiguous bytes of a row).
 __device__ __forceinline__ void opnd_chunk(double (&v)[kSteps], const Opnd64& o, int64_t sm,
                                            int64_t sk, int m, int mn, int k0, int K) {
   const int g = lane_id() >> 4;
   if (!o.p) {
 #pragma unroll
-    for (int q = 0; q < kSteps; ++q) v[q] = m < mn && k0 + 16 * g + q < K ? 1.0 : 0.0;
+    for (int q = 0; q < kSteps; ++q) v[q] = m < mn && k0 + 4 * q + g < K ? 1.0 : 0.0;
   } else if (o.dbl) {
 #pragma unroll
     for (int q = 0; q < kSteps; ++q) {
-      const int k = k0 + 16 * g + q;
+      const int k = k0 + 4 * q + g;
       v[q] = opnd_ld<double>(o.p, m * sm + k * sk, m < mn && k < K);
     }
   } else {
 #pragma unroll
     for (int q = 0; q < kSteps; ++q) {
-      const int k = k0 + 16 * g + q;
+      const int k = k0 + 4 * q + g;
       v[q] = opnd_ld<float>(o.p, m * sm + k * sk, m < mn && k < K);
     }
   }
