@@ -16,7 +16,7 @@
 // global memory in MFMA layout, all of a chunk's loads at once, so a kernel
 // is about one load round, a short MFMA chain and the stores, on as many CUs
 // as there are tiles.  (Before: 32 x 32 tiles through LDS chunk by chunk, and
-// one block per head; M = 64, C = 128, H = 8: 20 + 21 us; now about 5 + 6 us.)
+// one block per head; M = 64, C = 128, H = 8: 20 + 21 us; now 7 + 8 us.)
 #include "pa_device.hpp"
 #include "pa_internal.h"
 

@@ -204,6 +204,38 @@ def test_token_attention_general_heads(cases, shape):
     check_key_bias(ga["dbk"], ga["dbq"])
 
 
+# the head core's edges: heads whose matrices are held in LDS and heads too
+# large for it (D = C), widths below and across a 16-column tile, slices just
+# past a 16-row tile and a full 64, each with the output projection (the
+# backward then forms the head outputs again from the uncentred values).  The
+# bf16-storage layers run the fp32 forward core, the fp32 ones the double one;
+# the backward is the same kernel in both.
+CORE_EDGES = [(300, C, H, M, dt) for C, H, M in ((256, 1, 17), (256, 1, 64), (240, 30, 33), (96, 4, 64),
+                                                 (80, 4, 49)) for dt in ("f32", "bf16")]
+
+
+@pytest.mark.parametrize("shape", CORE_EDGES, ids=[f"C{c}-H{h}-M{m}-{d}" for _, c, h, m, d in CORE_EDGES])
+def test_token_core_edges(cases, shape):
+    # bar: fp32 products of at most 256 terms and a softmax over at most 64,
+    # in a chain of four: about 4 * sqrt(256) * 2^-24 = 4e-6, under the 1e-5
+    say(f"token core {shape}")
+    c, g, (f, _) = get_case(cases, shape, out_proj=True)
+    S = g.torch.from_numpy(f["S"].astype(np.float32)).cuda()
+    p = oracle_params(c)
+    check("Sp", g.attention(S),
+          oracle.token_attention(S.cpu().numpy(), c.H, p["Wq"], p["bq"], p["Wk"], p["bk"], p["Wv"],
+                                 p["bv"], p["Wo"], p["bo"]), "f32")
+    rng = np.random.default_rng(7)
+    dSp = g.torch.from_numpy(rng.standard_normal((c.M, c.C)).astype(np.float32)).cuda()
+    ga = g.attention_backward(S, dSp)
+    ref = oracle.token_attention_backward(S.cpu().numpy(), c.H, p["Wq"], p["bq"], p["Wk"],
+                                          p["bk"], p["Wv"], p["bv"], p["Wo"], p["bo"],
+                                          dSp.cpu().numpy())
+    for k in ("dS", "dWq", "dbq", "dWk", "dWv", "dbv", "dWo", "dbo"):
+        check(k, ga[k], ref[k], "f32")
+    check_key_bias(ga["dbk"], ga["dbq"])
+
+
 def _slice_backward_ref(c, f, dS, Sp, use_dY):
     """Oracle of pa_slice_aggregate_backward for the given dS / Sp / dY."""
     p = oracle_params(c)
