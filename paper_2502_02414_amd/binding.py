@@ -163,10 +163,26 @@ def _ptr(t) -> Optional[int]:
     return t.data_ptr()
 
 
+class _Codes(dict):
+    """torch dtype -> PA_* code (None: unsupported), filled at its first use."""
+
+    def __missing__(self, dtype):
+        import torch
+        self.update({torch.float32: PA_F32, torch.bfloat16: PA_BF16})
+        return self.get(dtype)
+
+
+_codes = _Codes()
+
+
 # Element-count and dtype checks against the dims of a call: the library
 # only sees pointers, so a tensor smaller than the shape it stands for would
 # be read or written past its end.  A requirement is (elements, dtype), the
 # dtype a PA_* code, or None for "fp32 or the storage dtype" (not checked).
+# Every call makes every check: on the smallest fields (N = 4,096) the three
+# calls of a layer forward are bound by this host work, so a check that holds
+# takes one comparison of what the tensor reports with the requirement, and
+# only one that fails goes on to find out what to say.
 def _need(t, n: int, dt: Optional[int], name: str):
     if t is None:
         return
@@ -179,7 +195,10 @@ def _need(t, n: int, dt: Optional[int], name: str):
 
 def _arg(t, n: int, dt: Optional[int], name: str) -> Optional[int]:
     """Pointer of t after checking it against (n elements, dtype dt)."""
-    _need(t, n, dt, name)
+    if t is None:
+        return None
+    if t.numel() < n or (dt is not None and _codes[t.dtype] != dt):
+        _need(t, n, dt, name)
     return _ptr(t)
 
 
@@ -187,21 +206,26 @@ def _check_struct(st, dims, heads: int = 1, stacked: bool = False):
     """Checks the tensors a parameter struct was made from against dims
     (structs built by the make_* helpers below carry their tensors);
     ``stacked``: every tensor holds one block per head."""
-    for name, (t, kind) in getattr(st, "_tensors", {}).items():
-        n = _struct_count(kind, dims, heads) * (heads if stacked else 1)
-        _need(t, n, _struct_dtype(kind, dims), name)
-
-
-def _struct_count(kind: str, d, heads: int) -> int:
-    C, M = d.C, d.M
-    return {"CM": C * M, "CM32": C * M, "M": M, "C": C, "C32": C, "1": 1, "CC": C * C,
-            "hCM": heads * C * M, "hCM32": heads * C * M, "hM": heads * M, "hC": heads * C,
-            "hC32": heads * C, "h": heads}[kind]
-
-
-def _struct_dtype(kind: str, d) -> Optional[int]:
+    tensors = getattr(st, "_tensors", None)
+    if not tensors:
+        return
+    C, M, dt = dims.C, dims.M, dims.dtype
+    if stacked:  # (a struct's dims factor: every count below is a product with one of them)
+        C1, M1, one = heads * C, heads * M, heads
+    else:
+        C1, M1, one = C, M, 1
     # A and a are in the storage dtype; everything else in the structs is fp32
-    return {"CM": d.dtype, "C": d.dtype, "hCM": d.dtype, "hC": d.dtype}.get(kind, PA_F32)
+    need = {"CM": (C1 * M, dt), "CM32": (C1 * M, PA_F32), "M": (M1, PA_F32), "C": (C1, dt),
+            "C32": (C1, PA_F32), "1": (one, PA_F32), "CC": (C1 * C, PA_F32)}
+    if isinstance(st, pa_heads_params):
+        h = heads * one
+        need.update({"hCM": (h * C * M, dt), "hCM32": (h * C * M, PA_F32), "hM": (h * M, PA_F32),
+                     "hC": (h * C, dt), "hC32": (h * C, PA_F32), "h": (h, PA_F32)})
+    codes = _codes
+    for name, (t, kind) in tensors.items():
+        n, want = need[kind]
+        if t.numel() < n or codes[t.dtype] != want:
+            _need(t, n, want, name)
 
 
 def _with(st, **tensors):
@@ -209,10 +233,26 @@ def _with(st, **tensors):
     return st
 
 
+_raw_stream = _device = None
+
+
+def _current_stream() -> int:
+    """The handle of torch's current stream.  torch.cuda.current_stream() is
+    asked once (it sets torch's GPU side up, or says that there is none);
+    after that the handle alone, without the Stream object around it."""
+    global _raw_stream, _device
+    if _raw_stream is None:
+        import torch
+        torch.cuda.current_stream()
+        _device = torch._C._cuda_getDevice
+        _raw_stream = torch._C._cuda_getCurrentRawStream
+    return _raw_stream(_device())
+
+
 def _stream(stream=None) -> Optional[int]:
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is None:
+        return _current_stream()
+    return stream.cuda_stream
 
 
 def make_dims(N: int, C: int, H: int, M: int, tau0: float, tau_min: float, eps: float,
@@ -250,8 +290,7 @@ def make_attn_grads(dWq=None, dbq=None, dWk=None, dbk=None, dWv=None, dbv=None, 
 def _shapes(dims, heads: int = 1) -> dict:
     """(elements, dtype) of the tensors of a layer call at these dims; with
     heads > 1 the point-side tensors and the states are stacked per head."""
-    N, C, M, dt = int(dims.N), int(dims.C), int(dims.M), int(dims.dtype)
-    h = int(heads)
+    N, C, M, dt, h = dims.N, dims.C, dims.M, dims.dtype, int(heads)
     return {"x": (h * N * C, dt), "G": (h * N * M, dt), "W32": (N * M, PA_F32),
             "N32": (N, PA_F32), "MC": (h * M * C, PA_F32), "M": (h * M, PA_F32)}
 
@@ -457,12 +496,10 @@ def _nbytes(t) -> int:
 
 
 def _dt(t) -> int:
-    import torch
-    if t.dtype == torch.bfloat16:
-        return PA_BF16
-    if t.dtype == torch.float32:
-        return PA_F32
-    raise ValueError(f"unsupported dtype {t.dtype}")
+    code = _codes[t.dtype]
+    if code is None:
+        raise ValueError(f"unsupported dtype {t.dtype}")
+    return code
 
 
 def pa_gemm(A, B, D, transA=False, transB=False, alpha=1.0, beta=0.0, bias=None, ws=None,
