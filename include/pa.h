@@ -357,8 +357,10 @@ pa_status pa_gelu_backward(int64_t n, pa_dtype dtype, const void* x, const void*
  * G [N,F] = GELU(X W1 + b1), X [N,K] and W1 [K,F] bf16, b1 [F] fp32,
  * K in {64, 128, 256}, F a positive multiple of 64, all pointers 16-byte
  * aligned.  GELU(u) = u Phi(u) is applied to the fp32 accumulator (to
- * within 1.7e-7 of its value) and rounded to bf16 once; the pre-activation u
- * is not written.  ws: at least 2 F K bytes, caller-owned (checked; its contents are not used).  bf16 only: with fp32
+ * within 3e-7 of its value, and to 1.5e-3 of it in the lower tail down to u =
+ * -12.9) and rounded to bf16 once; the pre-activation u is not written.  ws: at
+ * least 2 F K bytes, caller-owned (checked; its contents are not used).  bf16
+ * only: with fp32
  * storage the stack uses pa_gemm and pa_gelu.  Unserved K or F return
  * PA_ERR_UNSUPPORTED. */
 pa_status pa_mlp_up(int64_t N, int K, int F, const void* X, const void* W1, const float* b1,

@@ -50,44 +50,57 @@ namespace {
 // z = |x|, Q(z) = 1 - Phi(z) the upper tail, phi(z) = exp(-z^2 / 2) /
 // sqrt(2 pi).  The activation is the bulk of the kernel's VALU work (a
 // transcendental takes the time of four other instructions), so each uses one
-// exp2 and a polynomial; both were fitted for this kernel (weighted minimax,
-// linear programming over 2,000 points):
-//   log2 Q(z) as a polynomial of degree 7 on [0, 13] (Q decays like
-//     exp(-z^2 / 2), so its logarithm is smooth): error of z Q(z) at most
-//     1.7e-7, and relative to Q at most 8e-4 up to z = 5 (evaluated in fp32);
-//   Q(z) - z phi(z) = (z0 - z) exp2(p(z)), z0 its only root, p of degree 8 on
-//     [0, 13]: error at most 1.6e-7, relative at most 7e-4 for 2 < z < 5;
-//     GELU'(x) is then 1/2 + sign(x) (1/2 - (Q - z phi)).
-// Both are far below bf16's rounding step, which is what the results are
-// stored in.  (The rational erf of Abramowitz and Stegun 7.1.26, evaluated
-// the same way: 2.1e-7 and 1.7e-7, with a reciprocal more.)  The
-// clamp keeps the polynomials finite and propagates NaN (IEEE minimum);
-// GELU(+inf) = inf, GELU(-inf) = 0 (to 1e-33).
+// exp2 and a polynomial of the logarithm, which is smooth (both decay like
+// exp(-z^2 / 2)); fitted for this kernel over [0, 13.25] (weighted minimax,
+// linear programming over 3,000 points):
+//   Q(z) = exp2(p(z)), degree 10;
+//   Q(z) - z phi(z) = (z0 - z) exp2(p(z)), z0 its only root, degree 11; then
+//     GELU'(x) is 1 + v for x >= 0 and -v for x < 0, v = (z - z0) exp2(p).
+// bf16 keeps fp32's exponents, so the lower tails need their own digits: the
+// weights bound the relative error.  Evaluated in fp32 against 64 bits, x < 0:
+//   GELU   7.0e-7 for z < 1, 3.8e-5 up to 3, 2.4e-4 up to 5, 1.5e-3 up to 12.9
+//   GELU'  1.4e-7 absolute up to z = 3, 2.2e-5 up to 4, 5.1e-5 up to 6, 2.7e-4
+//          up to 13
+// and absolute at most 1.5e-7 and 1.1e-7 (x > 0: relative 5e-7 and 3e-7); half
+// a bf16 step is 2e-3 to 3.9e-3 of a value.  The rational erf of Abramowitz and Stegun
+// 7.1.26, evaluated the same way, has 7.0e-7, 5.2e-5, 1.6e-3, 3.7e-2 and, for
+// the slope, 3.0e-5, 1.0e-4, 2.3e-4, and takes a reciprocal more.  (Degrees 7
+// and 8 weighted by the absolute error alone, 374 and 638 us against 404 and
+// 678 us at N = 500,000, K = 256, F = 1024, lose all digits below x = -6.)
+// From z = 13 exp2 has no normal result and both are 0 (below 1e-36; slope 1
+// for x > 0).  The clamp keeps the polynomials finite and propagates NaN (IEEE
+// minimum): GELU(+inf) = inf, GELU(-inf) = 0.
 __device__ __forceinline__ float gelu_ap(float x) {
-  const float z = __builtin_elementwise_minimum(fabsf(x), 13.f);
-  float p = -4.718395132385922e-07f;
-  p = fmaf(p, z, 3.7946945667499676e-05f);
-  p = fmaf(p, z, -0.0007799809100106359f);
-  p = fmaf(p, z, 0.008062046952545643f);
-  p = fmaf(p, z, -0.05331820994615555f);
-  p = fmaf(p, z, -0.4588843584060669f);
-  p = fmaf(p, z, -1.1511520147323608f);
-  p = fmaf(p, z, -0.999998927116394f);
+  const float z = __builtin_elementwise_minimum(fabsf(x), 14.f);
+  float p = -1.005718064384098e-09f;
+  p = fmaf(p, z, 5.430629101965678e-08f);
+  p = fmaf(p, z, -1.151717242464656e-06f);
+  p = fmaf(p, z, 1.1231582902837545e-05f);
+  p = fmaf(p, z, -2.5174234906444326e-05f);
+  p = fmaf(p, z, -0.0005898026865907013f);
+  p = fmaf(p, z, 0.007740595377981663f);
+  p = fmaf(p, z, -0.05302676558494568f);
+  p = fmaf(p, z, -0.4590100646018982f);
+  p = fmaf(p, z, -1.1511328220367432f);
+  p = fmaf(p, z, -0.9999993443489075f);
   return fmaf(-z, fast_exp2(p), __builtin_elementwise_maximum(x, 0.f));
 }
 __device__ __forceinline__ float dgelu_ap(float x) {
-  const float z = __builtin_elementwise_minimum(fabsf(x), 13.f);
-  float p = 9.472704505242291e-07f;
-  p = fmaf(p, z, -3.0266723115346394e-05f);
-  p = fmaf(p, z, 0.0003959344467148185f);
-  p = fmaf(p, z, -0.0029573675710707903f);
-  p = fmaf(p, z, 0.014786088839173317f);
-  p = fmaf(p, z, -0.0547993965446949f);
-  p = fmaf(p, z, -0.560700535774231f);
-  p = fmaf(p, z, -0.38318517804145813f);
-  p = fmaf(p, z, -0.5884048342704773f);
-  const float h = fmaf(z - 0.7517915246935645f, fast_exp2(p), 0.5f);
-  return 0.5f + __builtin_copysignf(h, x);
+  const float z = __builtin_elementwise_minimum(fabsf(x), 14.f);
+  float p = -1.0389065302485179e-10f;
+  p = fmaf(p, z, 7.800505130717283e-09f);
+  p = fmaf(p, z, -2.573670201400091e-07f);
+  p = fmaf(p, z, 4.93322613692726e-06f);
+  p = fmaf(p, z, -6.138220487628132e-05f);
+  p = fmaf(p, z, 0.0005271713016554713f);
+  p = fmaf(p, z, -0.003265825565904379f);
+  p = fmaf(p, z, 0.015184481628239155f);
+  p = fmaf(p, z, -0.05506233870983124f);
+  p = fmaf(p, z, -0.5606260299682617f);
+  p = fmaf(p, z, -0.3831914961338043f);
+  p = fmaf(p, z, -0.5884047746658325f);
+  const float v = (z - 0.7517915246935644f) * fast_exp2(p);
+  return x < 0.f ? -v : 1.f + v;
 }
 
 // NCT 16-column tiles per wave.

@@ -26,6 +26,8 @@ bf16, and in a deep stack the backward carries that into every gradient
 below the block.  Without clamped points (the Ada-Temp projection scaled by
 0.05) and in fp32 every output is pinned.
 """
+import math
+
 import numpy as np
 import pytest
 
@@ -181,6 +183,36 @@ def test_mlp_up_non_finite():
         assert np.abs(dU[:, j] - dg[:, j]).max() < 2e-2 * np.abs(dg).max()
     assert np.isfinite(np.delete(G, [3, 40], axis=1)).all()
     assert np.isfinite(np.delete(dU, 40, axis=1)).all()
+
+
+def test_mlp_up_tails():
+    """GELU and its slope themselves, u = b1 (X = 0) and dY W2^T = 1, to a
+    relative error over [-12.5, 12.5]: they fall to 1e-34 in the lower tail,
+    where a bf16 result still has all its digits.  Bars: bf16 rounding
+    (2^-8 of the value), 2e-3 for GELU's upper-tail polynomial and 4e-4 for the slope's
+    (whose root at -0.75 leaves the fp32 rounding of its two terms, 2e-7)."""
+    import torch
+    N, K, F = 33, 64, 16384
+    say(f"mlp_up tails N={N} K={K} F={F}")
+    u = np.linspace(-12.5, 12.5, F).astype(np.float32)
+    dY, W2 = np.zeros((N, K), np.float32), np.zeros((F, K), np.float32)
+    dY[:, 0] = W2[:, 0] = 1
+    z = torch.zeros(N, K, dtype=torch.bfloat16, device="cuda")
+    W1 = torch.zeros(K, F, dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(2 * F * K, dtype=torch.uint8, device="cuda")
+    G, dU = dev(np.zeros((N, F)), "bf16"), dev(np.zeros((N, F)), "bf16")
+    B.pa_mlp_up(z, W1, dev(u), G, ws)
+    B.pa_mlp_up_backward(z, W1, dev(u), dev(dY, "bf16"), dev(W2, "bf16"), dU, ws)
+    x = u.astype(np.float64)
+    Phi = 0.5 * np.array([math.erfc(-v / math.sqrt(2)) for v in x])
+    phi = np.exp(-0.5 * x * x) / math.sqrt(2 * math.pi)
+    for name, got, ref, rel, fixed in (("G", G, x * Phi, 2e-3, 0.0),
+                                       ("dU", dU, Phi + x * phi, 4e-4, 2e-7)):
+        got = host(got)
+        assert np.array_equal(got, np.broadcast_to(got[0], got.shape)), name
+        err = np.abs(got[0] - ref) / ((2.0 ** -8 + rel) * np.abs(ref) + fixed)
+        say(f"  {name:10s} largest error {err.max():.2f} of its bar, at u = {x[err.argmax()]:.3f}")
+        assert err.max() <= 1, (name, err.max(), x[err.argmax()])
 
 
 GEMMS = [  # m, n, k, transA, transB, in dtype, out dtype, bias, residual
