@@ -8,11 +8,11 @@
 
 #include <cstdint>
 #include <cstring>
-#include <map>
 #include <mutex>
 #include <tuple>
 #include <utility>
 
+#include "pa_algo_cache.hpp"
 #include "pa_internal.h"
 
 namespace pa {
@@ -37,15 +37,15 @@ hipblasStatus_t handle_for_current_device(hipblasLtHandle_t* h) {
 
 hipDataType hip_type(int dtype) { return dtype == 1 ? HIP_R_16BF : HIP_R_32F; }
 
-// Algorithm choice cached per problem (shape, types, transposes, bias).
+// Algorithm choice cached per problem (shape, types, transposes, bias; workspace).
 constexpr int kTune = 8;  // heuristic candidates timed on a problem's first call
 // split-K of long reductions: K >= kSplitMinK, output <= kSplitMaxOut bytes,
 // up to kSplitMax partials of about kSplitRows rows each
 constexpr int64_t kSplitMinK = 1 << 17, kSplitRows = 1 << 14;
 constexpr size_t kSplitMaxOut = 8u << 20;
 constexpr int kSplitMax = 64;
-using Key = std::tuple<int, int, int64_t, int64_t, int64_t, int, int, int, int, bool, int>;
-std::map<Key, hipblasLtMatmulAlgo_t> g_algo;
+using Key = std::tuple<int, int, int64_t, int64_t, int64_t, int, int, int, int, bool>;
+AlgoCache<Key, hipblasLtMatmulAlgo_t> g_algo;
 
 struct Descs {
   hipblasLtMatmulDesc_t op = nullptr;
@@ -114,18 +114,9 @@ static int gemm_once(const Gemm& g, int batch, int64_t sa, int64_t sb, int64_t s
   int dev = 0;
   (void)hipGetDevice(&dev);
   const Key key{dev, (int)g.transA * 2 + (int)g.transB, g.m, g.n, g.k, g.ta, g.tb, g.td,
-                (g.beta != 0.f ? 1 : 0) + 2 * batch, g.bias != nullptr, (int)(g.ws_bytes >> 20)};
+                (g.beta != 0.f ? 1 : 0) + 2 * batch, g.bias != nullptr};
   hipblasLtMatmulAlgo_t algo;
-  bool have = false;
-  {
-    std::lock_guard<std::mutex> lk(g_mu);
-    auto it = g_algo.find(key);
-    if (it != g_algo.end()) {
-      algo = it->second;
-      have = true;
-    }
-  }
-  if (!have || tune) {
+  if (!g_algo.find(key, g.ws_bytes, &algo) || tune) {
     PA_LT(hipblasLtMatmulPreferenceCreate(&d.pref));
     uint64_t wmax = g.ws_bytes;
     PA_LT(hipblasLtMatmulPreferenceSetAttribute(d.pref, HIPBLASLT_MATMUL_PREF_MAX_WORKSPACE_BYTES,
@@ -133,9 +124,10 @@ static int gemm_once(const Gemm& g, int batch, int64_t sa, int64_t sb, int64_t s
     hipblasLtMatmulHeuristicResult_t res[kTune];
     int n = 0;
     PA_LT(hipblasLtMatmulAlgoGetHeuristic(h, d.op, d.a, d.b, d.d, d.d, d.pref, kTune, res, &n));
-    int best = -1;
-    for (int i = 0; i < n && best < 0; ++i)
-      if (res[i].state == HIPBLAS_STATUS_SUCCESS) best = i;
+    // (the library is asked for what fits the workspace; checked all the same)
+    auto ok = [&](int i) { return res[i].state == HIPBLAS_STATUS_SUCCESS; };
+    auto need = [&](int i) { return res[i].workspaceSize; };
+    int best = first_fit(n, g.ws_bytes, ok, need);
     if (best < 0) return (int)HIPBLAS_STATUS_NOT_SUPPORTED;
     // Tuning times the candidates once (synchronising the stream) and keeps
     // the fastest -- only when rerunning the product is harmless, i.e. D is
@@ -147,7 +139,7 @@ static int gemm_once(const Gemm& g, int batch, int64_t sa, int64_t sb, int64_t s
         const float al = g.alpha, be = g.beta;
         float best_ms = 1e30f;
         for (int i = 0; i < n; ++i) {
-          if (res[i].state != HIPBLAS_STATUS_SUCCESS) continue;
+          if (!ok(i) || need(i) > g.ws_bytes) continue;
           (void)hipEventRecord(e0, st);
           const hipblasStatus_t r = hipblasLtMatmul(h, d.op, &al, g.B, d.a, g.A, d.b, &be,
                                                     g.Cin ? g.Cin : g.D, d.d, g.D, d.d,
@@ -165,8 +157,7 @@ static int gemm_once(const Gemm& g, int batch, int64_t sa, int64_t sb, int64_t s
       }
     }
     algo = res[best].algo;
-    std::lock_guard<std::mutex> lk(g_mu);
-    g_algo[key] = algo;
+    g_algo.keep(key, g.ws_bytes, algo, need(best));
   }
   const float alpha = g.alpha, beta = g.beta;
   PA_LT(hipblasLtMatmul(h, d.op, &alpha, g.B, d.a, g.A, d.b, &beta, g.Cin ? g.Cin : g.D, d.d,
