@@ -296,19 +296,24 @@ pa_status pa_stream_probe(const pa_dims* dims, const char* call, const void* x,
 /* Row-major D[m,n] = alpha op(A) op(B) + beta C (+ bias[n] added to every
  * row), op(X) = X^T when trans; A is [m,k] ([k,m] when transA), B [k,n]
  * ([n,k] when transB); C [m,n] in D's dtype (nullable: C = D, in place;
- * a residual add when it is another tensor and beta = 1).  The plain GEMMs of the MLP and the linear layers,
- * on hipBLASLt (fp32 accumulation).  The first call on a device creates
- * one hipBLASLt handle there (kept until the process ends); ws/ws_bytes is
- * hipBLASLt's workspace (may be 0).  pa_gemm itself never synchronises: a
- * problem (shape, dtypes, transposes, bias) that pa_gemm_prepare has not
- * tuned runs hipBLASLt's first heuristic candidate.   A long reduction into a small
- * fp32 output (transA, beta = 0, no bias: the weight gradients) runs the
- * library's own kernel (A and B of one type, m and n multiples of 64, D at
- * most 8 MB; fp32 up to 2^17 points) or, from K = 2^17, hipBLASLt products
- * split over K.  Both keep up to 256 partial products at the end of ws (at
- * most half of it) and add them in order, deterministically; long
- * reductions want a workspace (64 MB serves every such product).  A combination of dtypes hipBLASLt does
- * not serve returns PA_ERR_UNSUPPORTED. */
+ * a residual add when it is another tensor and beta = 1).  The plain GEMMs
+ * of the MLP and the linear layers, on hipBLASLt (fp32 accumulation).  The
+ * first such call on a device creates one hipBLASLt handle there (kept until
+ * the process ends); ws/ws_bytes is scratch memory, clobbered (may be 0).
+ * pa_gemm itself never synchronises: a problem (shape, dtypes, transposes,
+ * bias) that pa_gemm_prepare has not tuned runs hipBLASLt's first heuristic
+ * candidate that fits ws.
+ * A reduction into a fp32 output of at most 8 MB (transA alone, beta = 0, no
+ * bias: the weight gradients) runs kernels of this library: where A and B are
+ * of one type and m and n multiples of 64, from k = 512 (outputs above 128 Ki
+ * elements: from 4,096 in bf16 and 16,384 in fp32) and up to 2^17 points in
+ * fp32; and from k = 512 for every shape and type where ws is below 1 MB.
+ * Other such products are hipBLASLt's, from k = 2^17 split over k.  Up to 256
+ * partial products lie at the end of ws (hipBLASLt's in at most half of it)
+ * and are added in order, deterministically: 64 MB serve every such product
+ * of this library's kernels, less takes longer, none several times as long.
+ * A combination of dtypes hipBLASLt does not serve returns
+ * PA_ERR_UNSUPPORTED. */
 pa_status pa_gemm(int transA, int transB, int64_t m, int64_t n, int64_t k, float alpha,
                   const void* A, pa_dtype a_dtype, const void* B, pa_dtype b_dtype,
                   float beta, const void* C, void* D, pa_dtype d_dtype, const float* bias,

@@ -96,6 +96,7 @@ static pa_status gemm_call(const char* who, bool tune, int transA, int transB, i
   g.bias = bias;
   g.ws = ws; g.ws_bytes = ws_bytes;
   const int s = pa::gemm(g, as_stream(stream), tune);
+  if (s < 0) PB_HIP((hipError_t)-s, who);
   if (s != 0)
     return err(s == 7 /* HIPBLAS_STATUS_NOT_SUPPORTED */ ? PA_ERR_UNSUPPORTED : PA_ERR_HIP,
                "%s: hipBLASLt status %d (m=%lld n=%lld k=%lld types %d,%d->%d)", who, s,

@@ -44,6 +44,9 @@ constexpr int kTune = 8;  // heuristic candidates timed on a problem's first cal
 constexpr int64_t kSplitMinK = 1 << 17, kSplitRows = 1 << 14;
 constexpr size_t kSplitMaxOut = 8u << 20;
 constexpr int kSplitMax = 64;
+// shortest reduction of our own kernels; a smaller workspace counts as none
+constexpr int64_t kOneMinK = 512;
+constexpr size_t kNoWs = 1 << 20;
 using Key = std::tuple<int, int, int64_t, int64_t, int64_t, int, int, int, int, bool>;
 AlgoCache<Key, hipblasLtMatmulAlgo_t> g_algo;
 
@@ -166,31 +169,38 @@ static int gemm_once(const Gemm& g, int batch, int64_t sa, int64_t sb, int64_t s
   return 0;
 }
 
+// D = the ordered sum of P partial products.
+static int add_parts(const Gemm& g, const float* parts, int P, hipStream_t st) {
+  Segments seg{};
+  seg.dst[0] = reinterpret_cast<float*>(g.D);
+  seg.len[0] = g.m * g.n;
+  seg.n = 1;
+  return -(int)launch_reduce(parts, P, g.m * g.n, seg, st);
+}
+
 int gemm(const Gemm& g, hipStream_t st, bool tune) {
-  // Weight gradients: the library's own kernel, its partial products at the
-  // end of the workspace (at most half of it) added in order into D; without
-  // room for two partials the product is one pass over the points, by few
-  // blocks and slower.  (hipBLASLt without a workspace is no alternative: its
-  // choice for 256 x 64 at k = 100,000 read out of range.)
+  // Weight gradients: kernels of our own.  The partial products of k_wgrad lie
+  // at the end of the workspace and are added in order into D.  With room for
+  // too few of them, and without a workspace for every type and shape, a long
+  // reduction is formed in one piece by k_wgrad_one.  (Not by hipBLASLt: its
+  // choice without a workspace for bf16 256 x 64 at k = 100,000 read out of
+  // range once, and what caused it is not known.)
   const size_t part = (size_t)g.m * g.n * sizeof(float);
   const bool wgrad_form = g.transA && !g.transB && g.td == 0 && g.beta == 0.f && !g.bias && !g.Cin;
-  if (wgrad_form && g.ta == g.tb && wgrad_served(g.m, g.n, g.k, g.ta)) {
-    const int64_t want = wgrad_splits(g.m, g.n, g.k, g.ta);
-    const int64_t most = g.ws ? (int64_t)(g.ws_bytes / 2 / part) : 0;
-    const int P = (int)(want <= most ? want : most > 1 ? most : 1);
-    float* parts = reinterpret_cast<float*>(g.D);
-    if (P > 1)
-      parts = reinterpret_cast<float*>(((uintptr_t)g.ws + g.ws_bytes - P * part) &
-                                       ~(uintptr_t)255);
-    if (launch_wgrad(g.m, g.n, g.k, g.alpha, g.A, g.B, g.ta, parts, P, st) != hipSuccess)
-      return (int)HIPBLAS_STATUS_EXECUTION_FAILED;
-    if (P == 1) return 0;
-    Segments seg{};
-    seg.dst[0] = reinterpret_cast<float*>(g.D);
-    seg.len[0] = g.m * g.n;
-    seg.n = 1;
-    return launch_reduce(parts, P, g.m * g.n, seg, st) == hipSuccess
-               ? 0 : (int)HIPBLAS_STATUS_EXECUTION_FAILED;
+  if (wgrad_form && g.k >= kOneMinK && part <= kSplitMaxOut) {
+    const uintptr_t ws0 = ((uintptr_t)g.ws + 255) & ~(uintptr_t)255, ws1 = (uintptr_t)g.ws + g.ws_bytes;
+    const int64_t most = g.ws && ws1 > ws0 ? (int64_t)((ws1 - ws0) / part) : 0;
+    const bool served = g.ta == g.tb && wgrad_served(g.m, g.n, g.k, g.ta);
+    const WgradPlan w = served ? wgrad_plan(g.m, g.n, g.k, g.ta, most) : WgradPlan{};
+    float* D = reinterpret_cast<float*>(g.D);
+    if (served && w.pays) {
+      float* parts = w.P > 1 ? reinterpret_cast<float*>((ws1 - w.P * part) & ~(uintptr_t)255) : D;
+      const hipError_t e = launch_wgrad(g.m, g.n, g.k, g.alpha, g.A, g.B, g.ta, parts, w, st);
+      if (e != hipSuccess) return -(int)e;
+      return w.P > 1 ? add_parts(g, parts, w.P, st) : 0;
+    }
+    if (served || g.ws_bytes < kNoWs)
+      return -(int)launch_wgrad_one(g.m, g.n, g.k, g.alpha, g.A, g.ta, g.B, g.tb, D, st);
   }
   // Other long reductions into a small fp32 output (outputs that are no whole
   // tiles, fp32 from 2^17 points, mixed types) are split over K: S
@@ -224,12 +234,7 @@ int gemm(const Gemm& g, hipStream_t st, bool tune) {
         r = gemm_once(t, 1, 0, 0, 0, st, tune);
         if (r) return r;
       }
-      Segments seg{};
-      seg.dst[0] = reinterpret_cast<float*>(g.D);
-      seg.len[0] = g.m * g.n;
-      seg.n = 1;
-      return launch_reduce(parts, P, g.m * g.n, seg, st) == hipSuccess
-                 ? 0 : (int)HIPBLAS_STATUS_EXECUTION_FAILED;
+      return add_parts(g, parts, P, st);
     }
   }
   return gemm_once(g, 1, 0, 0, 0, st, tune);

@@ -276,11 +276,21 @@ hipError_t launch_heads_sum(int H, int64_t L, int blockdiag, const float* src, f
 // alpha A^T B over its range of the k rows (A [k,m], B [k,n], both in dtype;
 // the sum over p is the product; P = 1: the product itself).
 bool wgrad_served(int64_t m, int64_t n, int64_t k, int dtype);
-int wgrad_splits(int64_t m, int64_t n, int64_t k, int dtype);
+struct WgradPlan {
+  int cap;    // tile edges are at most this
+  int P;      // splits of the points
+  bool pays;  // against the product in one piece (below)
+};
+// ... with room for at most `most` partials
+WgradPlan wgrad_plan(int64_t m, int64_t n, int64_t k, int dtype, int64_t most);
 hipError_t launch_wgrad(int64_t m, int64_t n, int64_t k, float alpha, const void* A,
-                        const void* B, int dtype, float* out, int P, hipStream_t st);
-// Row-major D[m,n] = alpha op(A) op(B) + beta D (+ bias[n]) on hipBLASLt;
-// dtypes 0 fp32, 1 bf16.  Returns 0 or a hipblasStatus_t.
+                        const void* B, int dtype, float* out, const WgradPlan& w, hipStream_t st);
+// The same in one piece, D [m,n] (m n at most 2^21), of any m, n, k and types.
+hipError_t launch_wgrad_one(int64_t m, int64_t n, int64_t k, float alpha, const void* A, int ta,
+                            const void* B, int tb, float* D, hipStream_t st);
+// Row-major D[m,n] = alpha op(A) op(B) + beta D (+ bias[n]) on hipBLASLt or,
+// for weight gradients, the kernels above; dtypes 0 fp32, 1 bf16.  Returns 0, a
+// hipblasStatus_t, or a hipError_t with its sign changed.
 struct Gemm {
   bool transA = false, transB = false;
   int64_t m = 0, n = 0, k = 0;

@@ -228,30 +228,228 @@ hipError_t launch_w(const WgradArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Tile edge along a dimension (a multiple of 64): the largest of 256, 128, 64
-// that divides it.  At most 128 in fp32 (the matrix cores bind it at any
-// tile) and for up to kShortK points in bf16, where blocks of four times as
-// many smaller tiles fill the chip sooner and leave fewer partials (1024 x
-// 256: k = 8,000 28 us against 39 us, k = 33,000 46 us against 58 us, k =
-// 131,072 140 us against 115 us).
-constexpr int64_t kShortK = 98304;
-int edge(int64_t v, int64_t k, int dtype) {
-  return v % 256 == 0 && k > kShortK && dtype == 1 ? 256 : v % 128 == 0 ? 128 : 64;
+// ---------------------------------------------------------------------------
+// The same product with no room for partial tiles, and of any m, n, k and
+// operand types: one block per 16 TI x 16 TI output tile over all points, its
+// waves on every WAVES-th chunk of 32 points, their sums added in wave order.
+// Operands go straight from global memory to the MFMA layout, chunks ahead:
+// lane (r, g) holds points 4 s + g, s < 8, of TI columns (the same points for
+// both operands), in one load of TI elements where the output is whole tiles
+// (WHOLE), else element by element with the columns clamped.  bf16 operands:
+// v_mfma_f32_16x16x32_bf16; otherwise fp32 MFMA, in which bf16 values are exact.
+// ---------------------------------------------------------------------------
+struct WgradOneArgs {
+  const void* A;  // [k, m]
+  const void* B;  // [k, n]
+  float* D;       // [m, n]
+  int64_t k, m, n;
+  float alpha;
+};
+
+template <int TI>
+struct OneGeo {
+  static constexpr int WAVES = TI == 1 ? 16 : TI == 2 ? 8 : 4;  // (the fewer, the more registers a lane)
+  static constexpr int DEEP = TI == 2 ? 2 : TI == 1 ? 4 : 3;   // chunks in flight and at work
+  static constexpr int LDS = WAVES * TI * TI * 64 * 16;
+};
+
+template <typename TA, typename TB, int TI, bool WHOLE>
+__global__ void __launch_bounds__(64 * OneGeo<TI>::WAVES) k_wgrad_one(WgradOneArgs a) {
+  constexpr int WAVES = OneGeo<TI>::WAVES, DEEP = OneGeo<TI>::DEEP;
+  constexpr bool BF = sizeof(TA) == 2 && sizeof(TB) == 2;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  f32x4* part = reinterpret_cast<f32x4*>(smem);  // [wave][tile][lane]
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = lane_id(), r = lane & 15, g = lane >> 4;
+  const int64_t m0 = (int64_t)blockIdx.y * 16 * TI, n0 = (int64_t)blockIdx.x * 16 * TI;
+  // Lane r's column of tile i: TI r + i (past the end: the last one; not
+  // stored), as a byte offset into a row; a chunk's address is a uniform row
+  // plus a 32-bit offset (m n <= 2^21, so 32 rows are below 2^28 bytes).
+  struct RowA { TA v[TI]; };
+  struct RowB { TB v[TI]; };
+  struct Chunk { RowA a[8]; RowB b[8]; };
+  const uint32_t lda = (uint32_t)a.m * sizeof(TA), ldb = (uint32_t)a.n * sizeof(TB);
+  uint32_t ca[TI], cb[TI];
+#pragma unroll
+  for (int i = 0; i < TI; ++i) {
+    ca[i] = (uint32_t)(WHOLE || m0 + TI * r + i < a.m ? m0 + TI * r + i : a.m - 1) * sizeof(TA);
+    cb[i] = (uint32_t)(WHOLE || n0 + TI * r + i < a.n ? n0 + TI * r + i : a.n - 1) * sizeof(TB);
+  }
+  auto row = [](auto& d, const char* p, uint32_t rows, const uint32_t (&c)[TI]) {
+    if constexpr (WHOLE) {
+      __builtin_memcpy(&d, p + (rows + c[0]), sizeof d);
+    } else {
+#pragma unroll
+      for (int i = 0; i < TI; ++i) __builtin_memcpy(&d.v[i], p + (rows + c[i]), sizeof d.v[i]);
+    }
+  };
+  auto load = [&](Chunk& v, int64_t c) {
+    const char* A = reinterpret_cast<const char*>(a.A) + 32 * c * lda;
+    const char* B = reinterpret_cast<const char*>(a.B) + 32 * c * ldb;
+    if (32 * c + 32 <= a.k) {
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        row(v.a[s], A, g * lda, ca);
+        row(v.b[s], B, g * ldb, cb);
+        A += 4 * lda;
+        B += 4 * ldb;
+        // (uniform: without this an address per row and column stays in
+        // registers, which spills; the one-load form is faster as it is)
+        if constexpr (!WHOLE) asm volatile("" : "+s"(A), "+s"(B));
+      }
+    } else {
+      const int last = (int)(a.k - 1 - 32 * c);  // (points past k: the last row)
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        const uint32_t p = 4 * s + g < last ? 4 * s + g : last;
+        row(v.a[s], A, p * lda, ca);
+        row(v.b[s], B, p * ldb, cb);
+      }
+    }
+  };
+  f32x4 acc[TI][TI];  // [n TI (4g + e) + j][m TI r + i]
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TI; ++j) acc[i][j] = zero4();
+  auto compute = [&](Chunk& v, int64_t c) {
+    if (32 * c + 32 > a.k) {  // points past k: zeros
+#pragma unroll
+      for (int s = 0; s < 8; ++s)
+        if (32 * c + 4 * s + g >= a.k) {
+          v.a[s] = RowA{};
+          v.b[s] = RowB{};
+        }
+    }
+    if constexpr (BF) {
+      K32<bf16> x[TI], y[TI];
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+          x[i].v[s] = v.a[s].v[i];
+          y[i].v[s] = v.b[s].v[i];
+        }
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TI; ++j) acc[i][j] = mma32(y[j], x[i], acc[i][j]);
+    } else {
+#pragma unroll
+      for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+          for (int j = 0; j < TI; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                to_f<TB>(v.b[s].v[j]), to_f<TA>(v.a[s].v[i]), acc[i][j], 0, 0, 0);
+    }
+  };
+  // the wave's chunks wave, wave + WAVES, .. through a ring of DEEP
+  const int64_t chunks = (a.k + 31) / 32;
+  Chunk v[DEEP];
+#pragma unroll
+  for (int d = 0; d + 1 < DEEP; ++d)
+    if (wave + d * WAVES < chunks) load(v[d], wave + d * WAVES);
+  for (int64_t c0 = wave; c0 < chunks; c0 += DEEP * WAVES) {
+#pragma unroll
+    for (int d = 0; d < DEEP; ++d) {
+      const int64_t c = c0 + d * WAVES, next = c + (DEEP - 1) * WAVES;
+      if (next < chunks) load(v[(d + DEEP - 1) % DEEP], next);
+      if (c < chunks) compute(v[d], c);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TI; ++j) part[(wave * TI * TI + i * TI + j) * 64 + lane] = acc[i][j];
+  __syncthreads();
+  for (int t = wave; t < TI * TI; t += WAVES) {
+    f32x4 x = part[t * 64 + lane];
+#pragma unroll
+    for (int q = 1; q < WAVES; ++q) x += part[(q * TI * TI + t) * 64 + lane];
+    const int64_t m = m0 + TI * r + t / TI;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int64_t n = n0 + TI * (4 * g + e) + t % TI;
+      if (WHOLE || (m < a.m && n < a.n)) a.D[m * a.n + n] = a.alpha * x[e];
+    }
+  }
 }
 
-}  // namespace
+template <typename TA, typename TB, int TI, bool WHOLE>
+hipError_t launch_one_t(const WgradOneArgs& a, hipStream_t st) {
+  const int e = 16 * TI;
+  const dim3 grid((unsigned)((a.n + e - 1) / e), (unsigned)((a.m + e - 1) / e));
+  hipLaunchKernelGGL((k_wgrad_one<TA, TB, TI, WHOLE>), grid, dim3(64 * OneGeo<TI>::WAVES),
+                     OneGeo<TI>::LDS, st, a);
+  return hipGetLastError();
+}
+
+// The largest tiles that still give half of the CUs a block: every one of them
+// reads all points.  (Bound by the load path and latency; bf16: 1024 x 512 at k
+// = 33,000, 128 blocks of 64 x 64: 207 us, 32 x 32: 306 us; 1024 x 256, 64 and
+// 256 blocks: 263 and 119 us; 512 x 128, k = 500,000, 64 blocks of 32 x 32 and
+// 256 of 16 x 16: 3.3 and 2.4 ms.)
+template <typename TA, typename TB>
+hipError_t launch_one(const WgradOneArgs& a, hipStream_t st) {
+  auto whole = [&](int e) { return a.m % e == 0 && a.n % e == 0; };
+  auto blocks = [&](int e) { return ((a.m + e - 1) / e) * ((a.n + e - 1) / e); };
+  if (whole(64) && blocks(64) >= 128) return launch_one_t<TA, TB, 4, true>(a, st);
+  if (blocks(32) >= 128)
+    return whole(32) ? launch_one_t<TA, TB, 2, true>(a, st) : launch_one_t<TA, TB, 2, false>(a, st);
+  return launch_one_t<TA, TB, 1, false>(a, st);
+}
+
+// Tile edge along a dimension (a multiple of 64): the largest of 256, 128, 64
+// up to cap that divides it.
+int edge(int64_t v, int cap) {
+  return cap >= 256 && v % 256 == 0 ? 256 : cap >= 128 && v % 128 == 0 ? 128 : 64;
+}
+int64_t tiles_of(int64_t m, int64_t n, int cap) { return (m / edge(m, cap)) * (n / edge(n, cap)); }
+
+// At most 128 in fp32 (the matrix cores bind it at any tile) and for up to
+// kShortK points in bf16, where blocks of four times as many smaller tiles fill
+// the chip sooner and leave fewer partials (1024 x 256: k = 8,000 28 us against
+// 39 us, k = 33,000 46 us against 58 us, k = 131,072 140 us against 115 us).
+constexpr int64_t kShortK = 98304;
+int largest_edge(int64_t k, int dtype) { return dtype == 1 && k > kShortK ? 256 : 128; }
 
 // Splits of the points: one block per CU at most, and no more than pay for
 // their partial tile.  A split costs a write and a read of m n floats (about
 // 8 m n bytes at 4 TB/s); the points cost k / 32 steps of about 0.5 us (fp32
 // 2 us) over the splits: P = sqrt(k / 32 x step / cost) minimises the sum.
-int wgrad_splits(int64_t m, int64_t n, int64_t k, int dtype) {
-  const int64_t tiles = (m / edge(m, k, dtype)) * (n / edge(n, k, dtype)), steps = (k + 31) / 32;
+int splits(int64_t m, int64_t n, int64_t k, int dtype, int cap) {
+  const int64_t tiles = tiles_of(m, n, cap), steps = (k + 31) / 32;
   const double cost_us = 8.0 * (double)m * (double)n / 4e6;
   int64_t P = (int64_t)std::sqrt((double)steps * (dtype == 1 ? 0.5 : 2.0) / cost_us);
   P = P < 256 / tiles ? P : 256 / tiles;
   P = P < steps ? P : steps;
   return (int)(P < 1 ? 1 : P);
+}
+
+}  // namespace
+
+// With room for fewer partials than the points are worth splitting into,
+// smaller tiles (while one block per CU takes them) make up for the blocks:
+// bf16 1024 x 256 at k = 500,000 with 1, 2, 4, 16 and 64 MB of workspace 1.9,
+// 1.9, 1.3, 0.52 and 0.34 ms (256 x 256 tiles alone, and with half of the
+// workspace: 12.0, 12.0, 6.1, 1.6 and 0.48 ms).  Below four partials the
+// product in one piece is faster (two: 2.5 ms against 1.9 ms; four: 1.3 ms)
+// unless larger tiles fill half of the CUs (1024 x 2048 at k = 100,000, 128
+// blocks: 1.2 ms against 1.6 ms).
+WgradPlan wgrad_plan(int64_t m, int64_t n, int64_t k, int dtype, int64_t most) {
+  WgradPlan w{largest_edge(k, dtype), 0, true};
+  w.P = splits(m, n, k, dtype, w.cap);
+  while (w.P > most && w.cap > 64 && tiles_of(m, n, w.cap / 2) * (most > 1 ? most : 1) <= 256) {
+    w.cap /= 2;
+    w.P = splits(m, n, k, dtype, w.cap);
+  }
+  if (w.P > 1 && w.P > most) {
+    w.P = most > 1 ? (int)most : 1;
+    w.pays = w.P >= 4 || (w.cap >= 128 && tiles_of(m, n, w.cap) * w.P >= 128);
+  }
+  return w;
 }
 
 // Whole 64 x 64 tiles, and lengths at which this kernel measured faster than
@@ -268,11 +466,12 @@ bool wgrad_served(int64_t m, int64_t n, int64_t k, int dtype) {
 }
 
 hipError_t launch_wgrad(int64_t m, int64_t n, int64_t k, float alpha, const void* A,
-                        const void* B, int dtype, float* out, int P, hipStream_t st) {
-  if (!wgrad_served(m, n, k, dtype) || P < 1 || P > (k + 31) / 32 || !A || !B || !out)
+                        const void* B, int dtype, float* out, const WgradPlan& w,
+                        hipStream_t st) {
+  if (!wgrad_served(m, n, k, dtype) || w.P < 1 || w.P > (k + 31) / 32 || !A || !B || !out)
     return hipErrorInvalidValue;
-  const WgradArgs a{A, B, out, k, (int)m, (int)n, P, alpha};
-  const int e = edge(m, k, dtype) * 1000 + edge(n, k, dtype);
+  const WgradArgs a{A, B, out, k, (int)m, (int)n, w.P, alpha};
+  const int e = edge(m, w.cap) * 1000 + edge(n, w.cap);
   if (dtype == 1) {
     switch (e) {
       case 256256: return launch_w<bf16, 256, 256>(a, st);
@@ -294,6 +493,14 @@ hipError_t launch_wgrad(int64_t m, int64_t n, int64_t k, float alpha, const void
     case 64064: return launch_w<float, 64, 64>(a, st);
     default: return hipErrorInvalidValue;
   }
+}
+
+hipError_t launch_wgrad_one(int64_t m, int64_t n, int64_t k, float alpha, const void* A, int ta,
+                            const void* B, int tb, float* D, hipStream_t st) {
+  if (m < 1 || n < 1 || k < 1 || m * n > (2 << 20) || !A || !B || !D) return hipErrorInvalidValue;
+  const WgradOneArgs a{A, B, D, k, m, n, alpha};
+  if (ta == 1) return tb == 1 ? launch_one<bf16, bf16>(a, st) : launch_one<bf16, float>(a, st);
+  return tb == 1 ? launch_one<float, bf16>(a, st) : launch_one<float, float>(a, st);
 }
 
 }  // namespace pa

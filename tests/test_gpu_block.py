@@ -264,6 +264,9 @@ WGRADS = [  # m, n, k, dtype, workspace bytes
     (256, 256, 98305, "bf16", 1 << 26), (256, 128, 98337, "bf16", 1 << 24),
     (64, 256, 98333, "bf16", 1 << 24), (128, 256, 100001, "bf16", 1 << 22),
     (512, 128, 3333, "bf16", 0), (256, 64, 100000, "bf16", 0),
+    # room for four partials, for two, and for no more than one (misaligned)
+    (1024, 256, 98337, "bf16", 1 << 22), (1024, 256, 98337, "bf16", 1 << 21),
+    (256, 256, 4097, "bf16", (1 << 19) + 100), (1024, 2048, 4097, "bf16", 0),
 ]
 
 
@@ -280,6 +283,28 @@ def test_weight_gradient(case):
     ws = torch.full((wsb,), 0xff, dtype=torch.uint8, device="cuda") if wsb else None
     B.pa_gemm(dev(A, dt), dev(Bm, dt), D, transA=True, alpha=0.5, ws=ws)
     check("D", host(D), 0.5 * (A.astype(np.float64).T @ Bm.astype(np.float64)), 1e-5)
+
+
+# the product in one piece (no workspace): its three tile sizes, whole and
+# ragged, ragged last chunks (k mod 32), every pair of operand types
+ONE_PIECE = [  # m, n, k, dtype of A, dtype of B
+    (16, 16, 512, "bf16", "bf16"), (1, 1, 513, "f32", "f32"), (100, 70, 4001, "bf16", "bf16"),
+    (65, 33, 1023, "f32", "bf16"), (64, 64, 131073, "f32", "f32"), (250, 1000, 2047, "bf16", "f32"),
+    (331, 501, 545, "bf16", "bf16"), (1024, 256, 1030, "bf16", "bf16"),
+    (1024, 512, 1030, "bf16", "bf16"), (1024, 512, 545, "f32", "f32"), (512, 1024, 513, "f32", "bf16"),
+]
+
+
+@pytest.mark.parametrize("case", ONE_PIECE, ids=["x".join(map(str, c)) for c in ONE_PIECE])
+def test_weight_gradient_in_one_piece(case):
+    """As above, in fp32 sums of at most 1e5 / 16 products each (1e-5)."""
+    import torch
+    m, n, k, ta, tb = case
+    say(f"weight gradient in one piece {case}")
+    A, Bm = _rnd(ta, k, m, seed=33), _rnd(tb, k, n, seed=34, shift=0.5)
+    D = torch.full((m, n), float("nan"), device="cuda")
+    B.pa_gemm(dev(A, ta), dev(Bm, tb), D, transA=True, alpha=-2.0)
+    check("D", host(D), -2.0 * (A.astype(np.float64).T @ Bm.astype(np.float64)), 1e-5)
 
 
 def test_colsum():
