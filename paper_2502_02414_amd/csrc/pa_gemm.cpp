@@ -181,16 +181,20 @@ static int add_parts(const Gemm& g, const float* parts, int P, hipStream_t st) {
 int gemm(const Gemm& g, hipStream_t st, bool tune) {
   // Weight gradients: kernels of our own.  The partial products of k_wgrad lie
   // at the end of the workspace and are added in order into D.  With room for
-  // too few of them, and without a workspace for every type and shape, a long
-  // reduction is formed in one piece by k_wgrad_one.  (Not by hipBLASLt: its
-  // choice without a workspace for bf16 256 x 64 at k = 100,000 read out of
-  // range once, and what caused it is not known.)
+  // too few of them, and without a workspace for every shape, a long reduction
+  // is formed in one piece by k_wgrad_one.  (Not by hipBLASLt: its choice
+  // without a workspace for bf16 256 x 64 at k = 100,000 read out of range
+  // once, and what caused it is not known.)  A and B of different types are
+  // left to hipBLASLt, which does not serve them: the answer must not depend on
+  // the workspace.
   const size_t part = (size_t)g.m * g.n * sizeof(float);
-  const bool wgrad_form = g.transA && !g.transB && g.td == 0 && g.beta == 0.f && !g.bias && !g.Cin;
+  const bool wgrad_form = g.transA && !g.transB && g.ta == g.tb && g.td == 0 && g.beta == 0.f &&
+                          !g.bias && !g.Cin;
   if (wgrad_form && g.k >= kOneMinK && part <= kSplitMaxOut) {
-    const uintptr_t ws0 = ((uintptr_t)g.ws + 255) & ~(uintptr_t)255, ws1 = (uintptr_t)g.ws + g.ws_bytes;
+    const uintptr_t ws0 = ((uintptr_t)g.ws + 255) & ~(uintptr_t)255;
+    const uintptr_t ws1 = (uintptr_t)g.ws + g.ws_bytes;
     const int64_t most = g.ws && ws1 > ws0 ? (int64_t)((ws1 - ws0) / part) : 0;
-    const bool served = g.ta == g.tb && wgrad_served(g.m, g.n, g.k, g.ta);
+    const bool served = wgrad_served(g.m, g.n, g.k, g.ta);
     const WgradPlan w = served ? wgrad_plan(g.m, g.n, g.k, g.ta, most) : WgradPlan{};
     float* D = reinterpret_cast<float*>(g.D);
     if (served && w.pays) {
@@ -200,14 +204,13 @@ int gemm(const Gemm& g, hipStream_t st, bool tune) {
       return w.P > 1 ? add_parts(g, parts, w.P, st) : 0;
     }
     if (served || g.ws_bytes < kNoWs)
-      return -(int)launch_wgrad_one(g.m, g.n, g.k, g.alpha, g.A, g.ta, g.B, g.tb, D, st);
+      return -(int)launch_wgrad_one(g.m, g.n, g.k, g.alpha, g.A, g.B, g.ta, D, st);
   }
   // Other long reductions into a small fp32 output (outputs that are no whole
-  // tiles, fp32 from 2^17 points, mixed types) are split over K: S
-  // strided-batched products of kc rows each (plus one for the rest) write S
-  // fp32 partials at the end of the workspace, added in order into D by the
-  // ordered reduction (deterministic; the whole GPU works on S times as many
-  // output tiles).
+  // tiles, fp32 from 2^17 points) are split over K: S strided-batched products
+  // of kc rows each (plus one for the rest) write S fp32 partials at the end of
+  // the workspace, added in order into D by the ordered reduction
+  // (deterministic; the whole GPU works on S times as many output tiles).
   if (wgrad_form && g.k >= kSplitMinK && part <= kSplitMaxOut && g.ws) {
     int S = (int)(g.k / kSplitRows);
     S = S < kSplitMax ? S : kSplitMax;

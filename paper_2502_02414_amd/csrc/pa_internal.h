@@ -285,9 +285,9 @@ struct WgradPlan {
 WgradPlan wgrad_plan(int64_t m, int64_t n, int64_t k, int dtype, int64_t most);
 hipError_t launch_wgrad(int64_t m, int64_t n, int64_t k, float alpha, const void* A,
                         const void* B, int dtype, float* out, const WgradPlan& w, hipStream_t st);
-// The same in one piece, D [m,n] (m n at most 2^21), of any m, n, k and types.
-hipError_t launch_wgrad_one(int64_t m, int64_t n, int64_t k, float alpha, const void* A, int ta,
-                            const void* B, int tb, float* D, hipStream_t st);
+// The same in one piece, D [m,n] (m n at most 2^21), of any m, n and k.
+hipError_t launch_wgrad_one(int64_t m, int64_t n, int64_t k, float alpha, const void* A,
+                            const void* B, int dtype, float* D, hipStream_t st);
 // Row-major D[m,n] = alpha op(A) op(B) + beta D (+ bias[n]) on hipBLASLt or,
 // for weight gradients, the kernels above; dtypes 0 fp32, 1 bf16.  Returns 0, a
 // hipblasStatus_t, or a hipError_t with its sign changed.

@@ -229,14 +229,13 @@ hipError_t launch_w(const WgradArgs& a, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------
-// The same product with no room for partial tiles, and of any m, n, k and
-// operand types: one block per 16 TI x 16 TI output tile over all points, its
-// waves on every WAVES-th chunk of 32 points, their sums added in wave order.
+// The same product with no room for partial tiles, and of any m, n and k: one
+// block per 16 TI x 16 TI output tile over all points, its waves on every
+// WAVES-th chunk of 32 points, their sums added in wave order.
 // Operands go straight from global memory to the MFMA layout, chunks ahead:
 // lane (r, g) holds points 4 s + g, s < 8, of TI columns (the same points for
 // both operands), in one load of TI elements where the output is whole tiles
-// (WHOLE), else element by element with the columns clamped.  bf16 operands:
-// v_mfma_f32_16x16x32_bf16; otherwise fp32 MFMA, in which bf16 values are exact.
+// (WHOLE), else element by element with the columns clamped.
 // ---------------------------------------------------------------------------
 struct WgradOneArgs {
   const void* A;  // [k, m]
@@ -253,10 +252,9 @@ struct OneGeo {
   static constexpr int LDS = WAVES * TI * TI * 64 * 16;
 };
 
-template <typename TA, typename TB, int TI, bool WHOLE>
+template <typename T, int TI, bool WHOLE>
 __global__ void __launch_bounds__(64 * OneGeo<TI>::WAVES) k_wgrad_one(WgradOneArgs a) {
   constexpr int WAVES = OneGeo<TI>::WAVES, DEEP = OneGeo<TI>::DEEP;
-  constexpr bool BF = sizeof(TA) == 2 && sizeof(TB) == 2;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   f32x4* part = reinterpret_cast<f32x4*>(smem);  // [wave][tile][lane]
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -265,17 +263,16 @@ __global__ void __launch_bounds__(64 * OneGeo<TI>::WAVES) k_wgrad_one(WgradOneAr
   // Lane r's column of tile i: TI r + i (past the end: the last one; not
   // stored), as a byte offset into a row; a chunk's address is a uniform row
   // plus a 32-bit offset (m n <= 2^21, so 32 rows are below 2^28 bytes).
-  struct RowA { TA v[TI]; };
-  struct RowB { TB v[TI]; };
-  struct Chunk { RowA a[8]; RowB b[8]; };
-  const uint32_t lda = (uint32_t)a.m * sizeof(TA), ldb = (uint32_t)a.n * sizeof(TB);
+  struct Row { T v[TI]; };
+  struct Chunk { Row a[8], b[8]; };
+  const uint32_t lda = (uint32_t)a.m * sizeof(T), ldb = (uint32_t)a.n * sizeof(T);
   uint32_t ca[TI], cb[TI];
 #pragma unroll
   for (int i = 0; i < TI; ++i) {
-    ca[i] = (uint32_t)(WHOLE || m0 + TI * r + i < a.m ? m0 + TI * r + i : a.m - 1) * sizeof(TA);
-    cb[i] = (uint32_t)(WHOLE || n0 + TI * r + i < a.n ? n0 + TI * r + i : a.n - 1) * sizeof(TB);
+    ca[i] = (uint32_t)(WHOLE || m0 + TI * r + i < a.m ? m0 + TI * r + i : a.m - 1) * sizeof(T);
+    cb[i] = (uint32_t)(WHOLE || n0 + TI * r + i < a.n ? n0 + TI * r + i : a.n - 1) * sizeof(T);
   }
-  auto row = [](auto& d, const char* p, uint32_t rows, const uint32_t (&c)[TI]) {
+  auto row = [](Row& d, const char* p, uint32_t rows, const uint32_t (&c)[TI]) {
     if constexpr (WHOLE) {
       __builtin_memcpy(&d, p + (rows + c[0]), sizeof d);
     } else {
@@ -317,11 +314,11 @@ __global__ void __launch_bounds__(64 * OneGeo<TI>::WAVES) k_wgrad_one(WgradOneAr
 #pragma unroll
       for (int s = 0; s < 8; ++s)
         if (32 * c + 4 * s + g >= a.k) {
-          v.a[s] = RowA{};
-          v.b[s] = RowB{};
+          v.a[s] = Row{};
+          v.b[s] = Row{};
         }
     }
-    if constexpr (BF) {
+    if constexpr (sizeof(T) == 2) {
       K32<bf16> x[TI], y[TI];
 #pragma unroll
       for (int i = 0; i < TI; ++i)
@@ -341,8 +338,8 @@ __global__ void __launch_bounds__(64 * OneGeo<TI>::WAVES) k_wgrad_one(WgradOneAr
         for (int i = 0; i < TI; ++i)
 #pragma unroll
           for (int j = 0; j < TI; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                to_f<TB>(v.b[s].v[j]), to_f<TA>(v.a[s].v[i]), acc[i][j], 0, 0, 0);
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(v.b[s].v[j], v.a[s].v[i], acc[i][j],
+                                                             0, 0, 0);
     }
   };
   // the wave's chunks wave, wave + WAVES, .. through a ring of DEEP
@@ -377,11 +374,11 @@ __global__ void __launch_bounds__(64 * OneGeo<TI>::WAVES) k_wgrad_one(WgradOneAr
   }
 }
 
-template <typename TA, typename TB, int TI, bool WHOLE>
+template <typename T, int TI, bool WHOLE>
 hipError_t launch_one_t(const WgradOneArgs& a, hipStream_t st) {
   const int e = 16 * TI;
   const dim3 grid((unsigned)((a.n + e - 1) / e), (unsigned)((a.m + e - 1) / e));
-  hipLaunchKernelGGL((k_wgrad_one<TA, TB, TI, WHOLE>), grid, dim3(64 * OneGeo<TI>::WAVES),
+  hipLaunchKernelGGL((k_wgrad_one<T, TI, WHOLE>), grid, dim3(64 * OneGeo<TI>::WAVES),
                      OneGeo<TI>::LDS, st, a);
   return hipGetLastError();
 }
@@ -391,14 +388,14 @@ hipError_t launch_one_t(const WgradOneArgs& a, hipStream_t st) {
 // = 33,000, 128 blocks of 64 x 64: 207 us, 32 x 32: 306 us; 1024 x 256, 64 and
 // 256 blocks: 263 and 119 us; 512 x 128, k = 500,000, 64 blocks of 32 x 32 and
 // 256 of 16 x 16: 3.3 and 2.4 ms.)
-template <typename TA, typename TB>
+template <typename T>
 hipError_t launch_one(const WgradOneArgs& a, hipStream_t st) {
   auto whole = [&](int e) { return a.m % e == 0 && a.n % e == 0; };
   auto blocks = [&](int e) { return ((a.m + e - 1) / e) * ((a.n + e - 1) / e); };
-  if (whole(64) && blocks(64) >= 128) return launch_one_t<TA, TB, 4, true>(a, st);
+  if (whole(64) && blocks(64) >= 128) return launch_one_t<T, 4, true>(a, st);
   if (blocks(32) >= 128)
-    return whole(32) ? launch_one_t<TA, TB, 2, true>(a, st) : launch_one_t<TA, TB, 2, false>(a, st);
-  return launch_one_t<TA, TB, 1, false>(a, st);
+    return whole(32) ? launch_one_t<T, 2, true>(a, st) : launch_one_t<T, 2, false>(a, st);
+  return launch_one_t<T, 1, false>(a, st);
 }
 
 // Tile edge along a dimension (a multiple of 64): the largest of 256, 128, 64
@@ -495,12 +492,11 @@ hipError_t launch_wgrad(int64_t m, int64_t n, int64_t k, float alpha, const void
   }
 }
 
-hipError_t launch_wgrad_one(int64_t m, int64_t n, int64_t k, float alpha, const void* A, int ta,
-                            const void* B, int tb, float* D, hipStream_t st) {
+hipError_t launch_wgrad_one(int64_t m, int64_t n, int64_t k, float alpha, const void* A,
+                            const void* B, int dtype, float* D, hipStream_t st) {
   if (m < 1 || n < 1 || k < 1 || m * n > (2 << 20) || !A || !B || !D) return hipErrorInvalidValue;
   const WgradOneArgs a{A, B, D, k, m, n, alpha};
-  if (ta == 1) return tb == 1 ? launch_one<bf16, bf16>(a, st) : launch_one<bf16, float>(a, st);
-  return tb == 1 ? launch_one<float, bf16>(a, st) : launch_one<float, float>(a, st);
+  return dtype == 1 ? launch_one<bf16>(a, st) : launch_one<float>(a, st);
 }
 
 }  // namespace pa

@@ -286,12 +286,11 @@ def test_weight_gradient(case):
 
 
 # the product in one piece (no workspace): its three tile sizes, whole and
-# ragged, ragged last chunks (k mod 32), every pair of operand types
-ONE_PIECE = [  # m, n, k, dtype of A, dtype of B
-    (16, 16, 512, "bf16", "bf16"), (1, 1, 513, "f32", "f32"), (100, 70, 4001, "bf16", "bf16"),
-    (65, 33, 1023, "f32", "bf16"), (64, 64, 131073, "f32", "f32"), (250, 1000, 2047, "bf16", "f32"),
-    (331, 501, 545, "bf16", "bf16"), (1024, 256, 1030, "bf16", "bf16"),
-    (1024, 512, 1030, "bf16", "bf16"), (1024, 512, 545, "f32", "f32"), (512, 1024, 513, "f32", "bf16"),
+# ragged, ragged last chunks (k mod 32)
+ONE_PIECE = [  # m, n, k, dtype
+    (16, 16, 512, "bf16"), (1, 1, 513, "f32"), (100, 70, 4001, "bf16"), (65, 33, 1023, "f32"),
+    (64, 64, 131073, "f32"), (250, 1000, 2047, "f32"), (331, 501, 545, "bf16"),
+    (1024, 256, 1030, "bf16"), (1024, 512, 1030, "bf16"), (1024, 512, 545, "f32"),
 ]
 
 
@@ -299,12 +298,27 @@ ONE_PIECE = [  # m, n, k, dtype of A, dtype of B
 def test_weight_gradient_in_one_piece(case):
     """As above, in fp32 sums of at most 1e5 / 16 products each (1e-5)."""
     import torch
-    m, n, k, ta, tb = case
+    m, n, k, dt = case
     say(f"weight gradient in one piece {case}")
-    A, Bm = _rnd(ta, k, m, seed=33), _rnd(tb, k, n, seed=34, shift=0.5)
+    A, Bm = _rnd(dt, k, m, seed=33), _rnd(dt, k, n, seed=34, shift=0.5)
     D = torch.full((m, n), float("nan"), device="cuda")
-    B.pa_gemm(dev(A, ta), dev(Bm, tb), D, transA=True, alpha=-2.0)
+    B.pa_gemm(dev(A, dt), dev(Bm, dt), D, transA=True, alpha=-2.0)
     check("D", host(D), -2.0 * (A.astype(np.float64).T @ Bm.astype(np.float64)), 1e-5)
+
+
+@pytest.mark.parametrize("wsb", [0, 1000, 1 << 24])
+@pytest.mark.parametrize("k", [256, 600])
+def test_products_of_two_types_are_refused(k, wsb):
+    """A and B of different types: no algorithm, whatever the workspace."""
+    import torch
+    say(f"products of two types k={k} workspace {wsb}")
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda") if wsb else None
+    for ta, tb in ((torch.float32, torch.bfloat16), (torch.bfloat16, torch.float32)):
+        A, Bm = torch.ones(k, 64, dtype=ta, device="cuda"), torch.ones(k, 64, dtype=tb, device="cuda")
+        D = torch.full((64, 64), 7.0, device="cuda")
+        with pytest.raises(B.PAError, match="types"):
+            B.pa_gemm(A, Bm, D, transA=True, ws=ws)
+        assert (D == 7).all()
 
 
 def test_colsum():
