@@ -306,8 +306,9 @@ pa_status pa_stream_probe(const pa_dims* dims, const char* call, const void* x,
  * A reduction into a fp32 output of at most 8 MB (transA alone, beta = 0, no
  * bias: the weight gradients) runs kernels of this library: where A and B are
  * of one type and m and n multiples of 64, from k = 512 (outputs above 128 Ki
- * elements: from 4,096 in bf16 and 16,384 in fp32) and up to 2^17 points in
- * fp32; and from k = 512 for every shape where ws is below 1 MB.
+ * elements: from 4,096 in bf16 and 16,384 in fp32; none above 256 Ki in fp32)
+ * and up to 2^17 points in fp32; and from k = 512 for every shape where ws is
+ * below 1 MB.
  * Other such products are hipBLASLt's, from k = 2^17 split over k.  Up to 256
  * partial products lie at the end of ws (hipBLASLt's in at most half of it)
  * and are added in order, deterministically: 64 MB serve every such product

@@ -171,6 +171,8 @@ static int gemm_once(const Gemm& g, int batch, int64_t sa, int64_t sb, int64_t s
 
 // D = the ordered sum of P partial products.
 static int add_parts(const Gemm& g, const float* parts, int P, hipStream_t st) {
+  if (g.m * g.n % 4 == 0)
+    return -(int)launch_add_parts(parts, P, g.m * g.n, reinterpret_cast<float*>(g.D), st);
   Segments seg{};
   seg.dst[0] = reinterpret_cast<float*>(g.D);
   seg.len[0] = g.m * g.n;
@@ -179,10 +181,11 @@ static int add_parts(const Gemm& g, const float* parts, int P, hipStream_t st) {
 }
 
 int gemm(const Gemm& g, hipStream_t st, bool tune) {
-  // Weight gradients: kernels of our own.  The partial products of k_wgrad lie
-  // at the end of the workspace and are added in order into D.  With room for
-  // too few of them, and without a workspace for every shape, a long reduction
-  // is formed in one piece by k_wgrad_one.  (Not by hipBLASLt: its choice
+  // Weight gradients: kernels of our own, where they are the better ones and
+  // where there is no workspace.  The partial products of k_wgrad lie at the end
+  // of the workspace and are added in order into D.  With room for too few of
+  // them, and for every other shape, a long reduction is formed in one piece by
+  // k_wgrad_one.  (Not by hipBLASLt: its choice
   // without a workspace for bf16 256 x 64 at k = 100,000 read out of range
   // once, and what caused it is not known.)  A and B of different types are
   // left to hipBLASLt, which does not serve them: the answer must not depend on
@@ -194,20 +197,21 @@ int gemm(const Gemm& g, hipStream_t st, bool tune) {
     const uintptr_t ws0 = ((uintptr_t)g.ws + 255) & ~(uintptr_t)255;
     const uintptr_t ws1 = (uintptr_t)g.ws + g.ws_bytes;
     const int64_t most = g.ws && ws1 > ws0 ? (int64_t)((ws1 - ws0) / part) : 0;
-    const bool served = wgrad_served(g.m, g.n, g.k, g.ta);
-    const WgradPlan w = served ? wgrad_plan(g.m, g.n, g.k, g.ta, most) : WgradPlan{};
+    const bool own = g.ws_bytes < kNoWs || wgrad_served(g.m, g.n, g.k, g.ta);
+    const bool whole = own && wgrad_whole(g.m, g.n, g.k, g.ta);
+    const WgradPlan w = whole ? wgrad_plan(g.m, g.n, g.k, g.ta, most) : WgradPlan{};
     float* D = reinterpret_cast<float*>(g.D);
-    if (served && w.pays) {
+    if (whole && w.pays) {
       float* parts = w.P > 1 ? reinterpret_cast<float*>((ws1 - w.P * part) & ~(uintptr_t)255) : D;
       const hipError_t e = launch_wgrad(g.m, g.n, g.k, g.alpha, g.A, g.B, g.ta, parts, w, st);
       if (e != hipSuccess) return -(int)e;
       return w.P > 1 ? add_parts(g, parts, w.P, st) : 0;
     }
-    if (served || g.ws_bytes < kNoWs)
+    if (own)
       return -(int)launch_wgrad_one(g.m, g.n, g.k, g.alpha, g.A, g.B, g.ta, D, st);
   }
   // Other long reductions into a small fp32 output (outputs that are no whole
-  // tiles, fp32 from 2^17 points) are split over K: S strided-batched products
+  // tiles, fp32 outputs above 256 Ki or from 2^17 points) are split over K: S strided-batched products
   // of kc rows each (plus one for the rest) write S fp32 partials at the end of
   // the workspace, added in order into D by the ordered reduction
   // (deterministic; the whole GPU works on S times as many output tiles).

@@ -275,7 +275,8 @@ hipError_t launch_heads_sum(int H, int64_t L, int blockdiag, const float* src, f
 // Weight gradients (pa_wgrad.hip): out [P][m][n] fp32, split p's part of
 // alpha A^T B over its range of the k rows (A [k,m], B [k,n], both in dtype;
 // the sum over p is the product; P = 1: the product itself).
-bool wgrad_served(int64_t m, int64_t n, int64_t k, int dtype);
+bool wgrad_whole(int64_t m, int64_t n, int64_t k, int dtype);   // can be formed so
+bool wgrad_served(int64_t m, int64_t n, int64_t k, int dtype);  // ... better than by hipBLASLt
 struct WgradPlan {
   int cap;    // tile edges are at most this
   int P;      // splits of the points
@@ -285,6 +286,9 @@ struct WgradPlan {
 WgradPlan wgrad_plan(int64_t m, int64_t n, int64_t k, int dtype, int64_t most);
 hipError_t launch_wgrad(int64_t m, int64_t n, int64_t k, float alpha, const void* A,
                         const void* B, int dtype, float* out, const WgradPlan& w, hipStream_t st);
+// D = the sum of P such parts of `outputs` floats, in order (outputs a multiple
+// of 4, at most 2^21; parts and D 16-byte aligned).
+hipError_t launch_add_parts(const float* parts, int P, int64_t outputs, float* D, hipStream_t st);
 // The same in one piece, D [m,n] (m n at most 2^21), of any m, n and k.
 hipError_t launch_wgrad_one(int64_t m, int64_t n, int64_t k, float alpha, const void* A,
                             const void* B, int dtype, float* D, hipStream_t st);

@@ -14,11 +14,11 @@
 // form; both MFMA operands are then read transposed (ds_read_b64_tr_b16;
 // fp32: rows as they are, v_mfma_f32_16x16x4_f32, bound by the matrix cores'
 // fp32 rate).
-// Measured, with the reduction, against strided-batched library products with
-// the same split: 1024 x 256 at k = 500,000 457 -> 354 us (the kernel alone
-// 260 us from idle, 4.9 TB/s; the clock falls under a run of such products),
-// k = 33,000 (one library product) 119 -> 46 us; 512 x 128 at k = 500,000
-// 237 -> 137 us; 256 x 64 170 -> 65 us.  HBM reads: the operands, once.
+// Measured in runs of one product, with the reduction, against strided-batched
+// library products with the same split: 1024 x 256 at k = 500,000 437 -> 300 us
+// (the kernel alone 260 us from idle, 4.9 TB/s; the clock falls under a run of
+// such products), k = 33,000 (one library product) 117 -> 39 us; 512 x 128 at k
+// = 500,000 219 -> 131 us; 256 x 64 170 -> 61 us.  HBM reads: the operands, once.
 #include <cmath>
 
 #include "pa_internal.h"
@@ -398,19 +398,71 @@ hipError_t launch_one(const WgradOneArgs& a, hipStream_t st) {
   return launch_one_t<T, 1, false>(a, st);
 }
 
+// ---------------------------------------------------------------------------
+// D = the sum of P partial products, in split order: G groups of threads per
+// output, each adding a range of the partials in fp64, their sums added in
+// group order.  Bound by reading the partials once; 16 bytes per lane.  (The
+// reduction of the block records, k_reduce, has 16 groups of one column each
+// and reads the last record again where there are fewer: with it a 1024 x 256
+// output took 25 us for 3 partials and 27 for 62, 2048 x 1024 183 us for 2; now
+// 3.5, 11 and 4.)
+// ---------------------------------------------------------------------------
+template <int G>
+__global__ void __launch_bounds__(256) k_add_parts(const f32x4* __restrict__ parts, int P,
+                                                   int64_t quads, f32x4* __restrict__ D) {
+  constexpr int Q = 256 / G;  // outputs of four columns per block
+  __shared__ f64x4 sums[G > 1 ? G - 1 : 1][Q];
+  const int q = threadIdx.x % Q, grp = threadIdx.x / Q;
+  const int64_t i = (int64_t)blockIdx.x * Q + q, ic = i < quads ? i : quads - 1;
+  const int p0 = P * grp / G, p1 = P * (grp + 1) / G;  // (P >= G: at least one)
+  f64x4 acc{0.0, 0.0, 0.0, 0.0};
+  for (int p = p0; p < p1; p += 4) {
+    f32x4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = parts[(int64_t)(p + u < p1 ? p + u : p1 - 1) * quads + ic];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (p + u < p1)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += (double)v[u][e];
+  }
+  if constexpr (G > 1) {
+    if (grp > 0) sums[grp - 1][q] = acc;
+    __syncthreads();
+    if (grp > 0) return;
+#pragma unroll
+    for (int g = 0; g + 1 < G; ++g) acc += sums[g][q];
+  }
+  if (i < quads) D[i] = f32x4{(float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]};
+}
+
+template <int G>
+hipError_t launch_add(const float* parts, int P, int64_t quads, float* D, hipStream_t st) {
+  constexpr int Q = 256 / G;
+  hipLaunchKernelGGL(k_add_parts<G>, dim3((unsigned)((quads + Q - 1) / Q)), dim3(256), 0, st,
+                     reinterpret_cast<const f32x4*>(parts), P, quads, reinterpret_cast<f32x4*>(D));
+  return hipGetLastError();
+}
+
 // Tile edge along a dimension (a multiple of 64): the largest of 256, 128, 64
-// up to cap that divides it.
+// up to cap that divides it.  (256 rows come with 256 columns only.)
 int edge(int64_t v, int cap) {
   return cap >= 256 && v % 256 == 0 ? 256 : cap >= 128 && v % 128 == 0 ? 128 : 64;
 }
 int64_t tiles_of(int64_t m, int64_t n, int cap) { return (m / edge(m, cap)) * (n / edge(n, cap)); }
 
-// At most 128 in fp32 (the matrix cores bind it at any tile) and for up to
-// kShortK points in bf16, where blocks of four times as many smaller tiles fill
-// the chip sooner and leave fewer partials (1024 x 256: k = 8,000 28 us against
-// 39 us, k = 33,000 46 us against 58 us, k = 131,072 140 us against 115 us).
-constexpr int64_t kShortK = 98304;
-int largest_edge(int64_t k, int dtype) { return dtype == 1 && k > kShortK ? 256 : 128; }
+// 256 x 256, 128 x 256 and 64 x 256 tiles in bf16 for rows of whole 256-column
+// tiles and at least 1.6e10 points x outputs.  Below that, blocks of smaller
+// tiles fill the chip sooner (us, tiles up to 128 and 256): 256 x 256, k = 131,072
+// 37 and 45; 1024 x 256, k = 50,000 51 and 54, k = 66,000 64 and 58; 2048 x 256, k =
+// 24,000 49 and 54, k = 33,000 63 and 58; 2048 x 512, k = 12,000 47 and 55, k =
+// 16,384 60 and 59; 2048 x 1024, k = 12,000 84 and 72, k = 50,000 313 and 207.  Tiles
+// of 256 x 128 and 256 x 64 gain nothing (1024 x 384, k = 100,000 133 and 143; 1024
+// x 192, k = 131,072 152 and 150), nor do any in fp32, which the matrix cores bind.
+constexpr double kWideWork = 1.6e10;
+int largest_edge(int64_t m, int64_t n, int64_t k, int dtype) {
+  return dtype == 1 && n % 256 == 0 && (double)k * (double)(m * n) >= kWideWork ? 256 : 128;
+}
 
 // Splits of the points: one block per CU at most, and no more than pay for
 // their partial tile.  A split costs a write and a read of m n floats (about
@@ -430,13 +482,13 @@ int splits(int64_t m, int64_t n, int64_t k, int dtype, int cap) {
 // With room for fewer partials than the points are worth splitting into,
 // smaller tiles (while one block per CU takes them) make up for the blocks:
 // bf16 1024 x 256 at k = 500,000 with 1, 2, 4, 16 and 64 MB of workspace 1.9,
-// 1.9, 1.3, 0.52 and 0.34 ms (256 x 256 tiles alone, and with half of the
+// 1.9, 1.2, 0.45 and 0.29 ms (256 x 256 tiles alone, and with half of the
 // workspace: 12.0, 12.0, 6.1, 1.6 and 0.48 ms).  Below four partials the
 // product in one piece is faster (two: 2.5 ms against 1.9 ms; four: 1.3 ms)
 // unless larger tiles fill half of the CUs (1024 x 2048 at k = 100,000, 128
 // blocks: 1.2 ms against 1.6 ms).
 WgradPlan wgrad_plan(int64_t m, int64_t n, int64_t k, int dtype, int64_t most) {
-  WgradPlan w{largest_edge(k, dtype), 0, true};
+  WgradPlan w{largest_edge(m, n, k, dtype), 0, true};
   w.P = splits(m, n, k, dtype, w.cap);
   while (w.P > most && w.cap > 64 && tiles_of(m, n, w.cap / 2) * (most > 1 ? most : 1) <= 256) {
     w.cap /= 2;
@@ -449,31 +501,43 @@ WgradPlan wgrad_plan(int64_t m, int64_t n, int64_t k, int dtype, int64_t most) {
   return w;
 }
 
-// Whole 64 x 64 tiles, and lengths at which this kernel measured faster than
-// the library product.  Outputs of up to 128 Ki elements (512 x 128): from k
-// = 512 (14 us against 21 us); larger ones (1024 x 256): from 4,096 in bf16
-// (k = 2,001 24 us against 21 us, 8,000 28 us against 36 us) and 16,384 in
-// fp32 (8,000 60 us against 52 us, 33,000 165 us against 233 us).  fp32 from
-// 2^17 points stays with the split library products (1024 x 256 at 131,072:
-// 574 us against 528 us), whose partial sums are also shorter there.
+// What k_wgrad can form: whole 64 x 64 tiles.
+bool wgrad_whole(int64_t m, int64_t n, int64_t k, int dtype) {
+  return m >= 64 && n >= 64 && m % 64 == 0 && n % 64 == 0 && m * n <= (2 << 20) && k >= 512 &&
+         (dtype == 1 || k < (1 << 17));
+}
+
+// ... and where it is the better product (us: hipBLASLt's, its candidates timed
+// or the heuristic's first one, and this kernel's with its reduction).
+// bf16: 512 x 256, k = 1,000 13, 15 and 10; 1024 x 256, k = 2,000 14, 20 and 14, k =
+// 4,096 18, 28 and 18; 1024 x 512, k = 4,096 25, 28 and 22; 2048 x 1024, k = 4,096
+// 35, 39 and 36, k = 33,000 184, 237 and 137.
+// fp32, up to 128 Ki outputs: 128 x 512, k = 2,000 12, 17 and 18, k = 8,000 30, 47
+// and 26; 512 x 256, k = 4,096 17, 25 and 28, k = 12,000 45, 81 and 40: slower where
+// short, but its fp64 sum of many partials is closer to the product (128 x 512, k =
+// 2,000: relative error 4.0e-7, 8.0e-7 and 1.5e-7).  1024 x 256: k = 12,000 65, 82
+// and 64, k = 16,384 90, 103 and 82.  1024 x 512: slower at every length (k = 8,000
+// 67, 68 and 82, k = 33,000 259, 326 and 286), as are larger ones.
+// From 2^17 points fp32 stays with the split library products, which are as fast
+// or faster (128 x 256, k = 131,072 88 and 83; 128 x 512 156 and 151; 512 x 256 247
+// and 285; 1024 x 256 468 and 556) and whose partial sums are shorter.
 bool wgrad_served(int64_t m, int64_t n, int64_t k, int dtype) {
-  if (m < 64 || n < 64 || m % 64 != 0 || n % 64 != 0 || m * n > (2 << 20)) return false;
-  if (m * n <= (1 << 17)) return k >= 512 && (dtype == 1 || k < (1 << 17));
-  return dtype == 1 ? k >= 4096 : k >= 16384 && k < (1 << 17);
+  const int64_t out = m * n;
+  if (!wgrad_whole(m, n, k, dtype)) return false;
+  if (out <= (1 << 17)) return true;
+  return dtype == 1 ? k >= 4096 : out <= (1 << 18) && k >= 16384;
 }
 
 hipError_t launch_wgrad(int64_t m, int64_t n, int64_t k, float alpha, const void* A,
                         const void* B, int dtype, float* out, const WgradPlan& w,
                         hipStream_t st) {
-  if (!wgrad_served(m, n, k, dtype) || w.P < 1 || w.P > (k + 31) / 32 || !A || !B || !out)
+  if (!wgrad_whole(m, n, k, dtype) || w.P < 1 || w.P > (k + 31) / 32 || !A || !B || !out)
     return hipErrorInvalidValue;
   const WgradArgs a{A, B, out, k, (int)m, (int)n, w.P, alpha};
   const int e = edge(m, w.cap) * 1000 + edge(n, w.cap);
   if (dtype == 1) {
     switch (e) {
       case 256256: return launch_w<bf16, 256, 256>(a, st);
-      case 256128: return launch_w<bf16, 256, 128>(a, st);
-      case 256064: return launch_w<bf16, 256, 64>(a, st);
       case 128256: return launch_w<bf16, 128, 256>(a, st);
       case 128128: return launch_w<bf16, 128, 128>(a, st);
       case 128064: return launch_w<bf16, 128, 64>(a, st);
@@ -490,6 +554,17 @@ hipError_t launch_wgrad(int64_t m, int64_t n, int64_t k, float alpha, const void
     case 64064: return launch_w<float, 64, 64>(a, st);
     default: return hipErrorInvalidValue;
   }
+}
+
+// Groups: as many as keep a thread's loads few (256 Ki outputs, 62 partials: one
+// group 12.5 us, 4 and 8 10.7, 16 11.4; 16 Ki outputs, 250 partials: 28, 8.2, 5.3
+// and 3.9; 2 Mi outputs, 4 partials: 5.1 with one group, 8.5 with 4).
+hipError_t launch_add_parts(const float* parts, int P, int64_t outputs, float* D, hipStream_t st) {
+  if (!parts || !D || P < 1 || outputs < 4 || outputs % 4 || outputs > (2 << 20))
+    return hipErrorInvalidValue;
+  return P >= 128 ? launch_add<16>(parts, P, outputs / 4, D, st)
+         : P >= 8 ? launch_add<8>(parts, P, outputs / 4, D, st)
+                  : launch_add<1>(parts, P, outputs / 4, D, st);
 }
 
 hipError_t launch_wgrad_one(int64_t m, int64_t n, int64_t k, float alpha, const void* A,
