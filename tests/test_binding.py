@@ -124,6 +124,137 @@ def test_small_or_mistyped_tensors_refused_before_the_call(fake):
     assert fake.calls == []
 
 
+# every tensor of every parameter and gradient struct: (helper, its keyword,
+# elements at the test's dims, in the storage dtype?), for one layer
+_CM, _CC = C * M, C * C
+STRUCT_FIELDS = (
+    [("make_slice_params", k, n, st) for k, n, st in
+     (("A", _CM, True), ("b", M, False), ("a", C, True), ("b_t_dev", 1, False))] +
+    [("make_slice_grads", k, n, False) for k, n in
+     (("dA", _CM), ("db", M), ("da", C), ("db_t", 1), ("dtau0", 1))] +
+    [("make_attn_params", k, _CC if k[0] == "W" else C, False) for k in
+     ("Wq", "Wk", "Wv", "Wo", "bq", "bk", "bv", "bo")] +
+    [("make_attn_grads", k, _CC if k[1] == "W" else C, False) for k in
+     ("dWq", "dWk", "dWv", "dWo", "dbq", "dbk", "dbv", "dbo")])
+HEADS = 3
+HEAD_FIELDS = [("A", _CM, True), ("b", M, False), ("a", C, True), ("b_t", 1, False)]
+
+
+def _struct(maker, key, t):
+    kw = {key: t}
+    if maker == "make_attn_params":  # (the three weights are positional)
+        kw = {**{w: _t(C, C) for w in ("Wq", "Wk", "Wv")}, **kw}
+    if maker in ("make_slice_params", "make_heads_params") and key != "A":
+        kw["A"] = _t(HEADS * _CM, dt=torch.bfloat16)
+    return getattr(B, maker)(**kw)
+
+
+def _refuses(st, key, dims, *args):
+    with pytest.raises(ValueError, match=rf"^{key}: "):
+        B._check_struct(st, dims, *args)
+
+
+@pytest.mark.parametrize("maker,key,n,storage", STRUCT_FIELDS,
+                         ids=[f"{f[0]}-{f[1]}" for f in STRUCT_FIELDS])
+def test_every_struct_field_is_checked(fake, maker, key, n, storage):
+    """One element short or of another type: refused by name; the exact size
+    and larger: taken.  Gradients of a per-head call: stacked head on head."""
+    dims = B.make_dims(N, C, H, M, 0.5, 0.01, 1e-5, B.PA_BF16)
+    dt, other = (torch.bfloat16, torch.float32) if storage else (torch.float32, torch.bfloat16)
+    for heads in (1, HEADS) if maker == "make_slice_grads" else (1,):
+        m, args = heads * n, (dims, heads, heads > 1)
+        for size in (m, m + 1):
+            B._check_struct(_struct(maker, key, _t(size, dt=dt)), *args)
+        _refuses(_struct(maker, key, _t(m - 1, dt=dt)), key, *args)
+        _refuses(_struct(maker, key, _t(m, dt=other)), key, *args)
+        with pytest.raises(ValueError, match="unsupported dtype"):
+            B._check_struct(_struct(maker, key, _t(m, dt=torch.float16)), *args)
+
+
+@pytest.mark.parametrize("key,n,storage", HEAD_FIELDS, ids=[f[0] for f in HEAD_FIELDS])
+@pytest.mark.parametrize("shared", [False, True])
+def test_every_head_parameter_is_checked(fake, key, n, storage, shared):
+    """A block per head, or one for all."""
+    dims = B.make_dims(N, C, 1, M, 0.5, 0.01, 1e-5, B.PA_BF16)
+    dt, other = (torch.bfloat16, torch.float32) if storage else (torch.float32, torch.bfloat16)
+    m = n if shared else HEADS * n
+
+    def make(t):
+        kw = {"A": _t(HEADS * _CM, dt=torch.bfloat16), key: t}
+        return B.make_heads_params(**kw, shared=shared)
+    for size in (m, m + 1):
+        B._check_struct(make(_t(size, dt=dt)), dims, HEADS)
+    _refuses(make(_t(m - 1, dt=dt)), key, dims, HEADS)
+    _refuses(make(_t(m, dt=other)), key, dims, HEADS)
+
+
+def test_argument_checks(fake):
+    assert B._arg(None, 10, B.PA_F32, "x") is None
+    assert B._arg(_t(10), 10, B.PA_F32, "x") == 4096
+    assert B._arg(_t(10, dt=torch.float16), 10, None, "x") == 4096  # (type not asked for)
+    with pytest.raises(ValueError, match="^x: 9 elements, the call needs 10"):
+        B._arg(_t(9), 10, B.PA_F32, "x")
+    with pytest.raises(ValueError, match="^x: dtype torch.float32 does not match the call's bf16"):
+        B._arg(_t(10), 10, B.PA_BF16, "x")
+    with pytest.raises(ValueError, match="unsupported dtype torch.float16"):
+        B._arg(_t(10, dt=torch.float16), 10, B.PA_F32, "x")
+
+
+def test_host_and_strided_tensors_refused():
+    with pytest.raises(ValueError, match="GPU"):
+        B._arg(_t(10), 10, B.PA_F32, "x")
+
+    class Strided:
+        is_cuda, dtype = True, torch.float32
+
+        def numel(self):
+            return 10
+
+        def is_contiguous(self):
+            return False
+    with pytest.raises(ValueError, match="contiguous"):
+        B._arg(Strided(), 10, B.PA_F32, "x")
+
+
+def test_no_stream_without_a_gpu(monkeypatch):
+    """torch's own error, every time: nothing is kept from a first call that
+    found no GPU."""
+    monkeypatch.setattr(B, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream",
+                        lambda *a: (_ for _ in ()).throw(RuntimeError("no GPU")))
+    for _ in range(2):
+        with pytest.raises(RuntimeError, match="no GPU"):
+            B._stream()
+    assert B._raw_stream is None
+
+
+@pytest.mark.gpu
+def test_calls_go_to_the_current_stream():
+    """Without a stream, torch's current one at the time of the call, of the
+    calling thread; with one, that one."""
+    import threading
+    say = lambda: torch.cuda.current_stream().cuda_stream
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    seen = []
+
+    def look():
+        seen.append((B._stream(), say()))
+    for _ in range(2):
+        look()
+        with torch.cuda.stream(a):
+            look()
+            with torch.cuda.stream(b):
+                look()
+                t = threading.Thread(target=look)
+                t.start()
+                t.join()
+            look()
+            assert B._stream(b) == b.cuda_stream
+        look()
+    assert all(got == want for got, want in seen), seen
+    assert len({got for got, _ in seen}) == 3
+
+
 def test_wrapper_calls_match_argtypes():
     """Every load().pa_*(...) call in the binding passes exactly as many
     arguments as the symbol's ctypes argtypes declare (read from the source,
