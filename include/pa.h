@@ -41,10 +41,10 @@
  *   N >= 1; 1 <= M <= 64; H >= 1 and C % H == 0; tau_min > 0; eps > 0;
  *   required pointers non-NULL; workspace large enough.  Served channel
  *   counts: C a multiple of 16 in [16, 256] (other C >= 1 return
- *   PA_ERR_UNSUPPORTED; C = 256 with M > 48 in fp32 does not fit the slice
+ *   PA_ERR_UNSUPPORTED; C > 128 with M > 32 in fp32 does not fit the slice
  *   backward's on-chip tables either).  Failures return PA_ERR_INVALID,
- *   PA_ERR_UNSUPPORTED or
- *   PA_ERR_WORKSPACE and set the thread-local message of pa_last_error().
+ *   PA_ERR_UNSUPPORTED or PA_ERR_WORKSPACE and set the thread-local message
+ *   of pa_last_error().
  *   A failed HIP launch returns PA_ERR_HIP with HIP's message.  Non-finite
  *   input values propagate; there are no device-side checks.
  */
@@ -366,9 +366,8 @@ pa_status pa_gelu_backward(int64_t n, pa_dtype dtype, const void* x, const void*
  * within 3e-7 of its value, and to 1.5e-3 of it in the lower tail down to u =
  * -12.9) and rounded to bf16 once; the pre-activation u is not written.  ws: at
  * least 2 F K bytes, caller-owned (checked; its contents are not used).  bf16
- * only: with fp32
- * storage the stack uses pa_gemm and pa_gelu.  Unserved K or F return
- * PA_ERR_UNSUPPORTED. */
+ * only: with fp32 storage the stack uses pa_gemm and pa_gelu.  Unserved K or F
+ * return PA_ERR_UNSUPPORTED. */
 pa_status pa_mlp_up(int64_t N, int K, int F, const void* X, const void* W1, const float* b1,
                     void* G, void* ws, size_t ws_bytes, void* stream);
 /* Its chain rule with the pre-activation recomputed from X:

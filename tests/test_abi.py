@@ -288,6 +288,23 @@ def test_struct_layouts_match_header(tmp_path):
 
 
 @fake_addresses
+@pytest.mark.parametrize("C,M,served", [(128, 64, True), (144, 32, True), (144, 33, False),
+                                        (256, 32, True), (256, 33, False), (256, 48, False)])
+def test_fp32_rows_wider_than_128_channels_go_backward_up_to_32_slices(lib, C, M, served):
+    """The backward tables of wider rows and 48 slices exceed the 160 KB of
+    LDS; the other passes take every M (a served call is stopped here by its
+    missing workspace)."""
+    d = _dims(C=C, H=1, M=M, dtype=B.PA_F32)
+    sp = B.pa_slice_params(FAKE, None, None, 0.0)
+    back = lib.pa_slice_aggregate_backward(ctypes.byref(d), FAKE, None, ctypes.byref(sp), FAKE,
+                                           FAKE, FAKE, None, None, FAKE, None, FAKE, 0, None)
+    assert back == (B.PA_ERR_WORKSPACE if served else B.PA_ERR_UNSUPPORTED)
+    agg = lib.pa_slice_aggregate(ctypes.byref(d), FAKE, None, ctypes.byref(sp), FAKE, FAKE, FAKE,
+                                 FAKE, 0, None)
+    assert agg == B.PA_ERR_WORKSPACE
+
+
+@fake_addresses
 def test_mlp_up_argument_checks(lib):
     F, K = 1024, 256
     # unserved K or F
