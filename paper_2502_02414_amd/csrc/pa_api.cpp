@@ -374,10 +374,11 @@ pa_status pa_slice_aggregate_w(const pa_dims* dims, const void* x, const void* G
 }  // extern "C"
 
 // ---------------------------------------------------------------------------
-// pa_slice_aggregate_noalloc: the aggregate's block records in a static
-// device array instead of a caller's workspace.  Each device holds its own copy of the array for the life of the process; host code
-// uses only the address hipGetSymbolAddress returns for it on that device
-// (the array's name is a host-side stand-in, not a device address).
+// pa_slice_aggregate_noalloc: the aggregate's block records in a static device
+// array instead of a caller's workspace.  Each device holds its own copy of the
+// array for the life of the process; host code uses only the address
+// hipGetSymbolAddress returns for it on that device (the array's name is a
+// host-side stand-in, not a device address).
 // ---------------------------------------------------------------------------
 namespace {
 constexpr size_t kNoallocScratchBytes = (size_t)17 << 20;  // 17 MiB

@@ -16,7 +16,6 @@ namespace pa {
 // that W in place of recomputing it from x and G.
 enum Pass { kAggregate = 0, kDeslice = 1, kDesliceBwd = 2, kWeights = 3, kSliceBwd = 4,
             kWeightsBwd = 5, kAggregateW = 6, kDesliceW = 7, kDesliceBwdW = 8 };
-constexpr int kNumPasses = 9;
 constexpr bool agg_fwd(int pass) { return pass == kAggregate || pass == kAggregateW; }
 constexpr bool agg_bwd(int pass) { return pass == kDesliceBwd || pass == kDesliceBwdW; }
 

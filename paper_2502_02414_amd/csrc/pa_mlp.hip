@@ -24,12 +24,14 @@
 // the next.  The F / (128 NCT) column blocks of one range of points are placed on
 // one XCD, so that h and dY come from HBM once and from that XCD's L2 after
 // that.
-// Measured at N = 500,000, K = 256, F = 1024 (one box): forward 503 -> 389 us,
-// backward 761 -> 650 us; N = 4,000 46 -> 13 and 85 -> 15 us; K = 128 219 ->
-// 166 and 305 -> 237 us.  (Before: weights staged chunk by chunk by every
-// block of 128 or 256 points, two barriers a chunk, and a rational erf.)
-// What bounds it now, from copies of the kernel with parts removed: backward
-// 690 us of events, without stores 612, without the activation 597, without
+// Measured in runs of one call at N = 500,000, K = 256, F = 1024: forward 503 ->
+// 424 us, backward 761 -> 677 us; N = 4,000 46 -> 13 and 85 -> 15 us; K = 128, F =
+// 512 219 -> 173 and 305 -> 238 us.  (Before: weights staged chunk by chunk by
+// every block of 128 or 256 points, two barriers a chunk, and a rational erf.)
+// Among the other products of a feed-forward layer, where the clock is lower,
+// 512 and 740 us under the profiler.
+// What bounds it, from copies of the kernel with parts removed (made with the
+// shorter polynomials named below): backward 690 us of events, without stores 612, without the activation 597, without
 // its loads 621, with only loads and LDS traffic 372; LDS (20 GB at 128 bytes
 // a clock and CU: 290 us), the matrix cores (240 us), the VALU (280 us) and
 // HBM (300 us) are about equally loaded and overlap in part.  Also tried:
@@ -65,8 +67,9 @@ namespace {
 // a bf16 step is 2e-3 to 3.9e-3 of a value.  The rational erf of Abramowitz and Stegun
 // 7.1.26, evaluated the same way, has 7.0e-7, 5.2e-5, 1.6e-3, 3.7e-2 and, for
 // the slope, 3.0e-5, 1.0e-4, 2.3e-4, and takes a reciprocal more.  (Degrees 7
-// and 8 weighted by the absolute error alone, 374 and 638 us against 404 and
-// 678 us at N = 500,000, K = 256, F = 1024, lose all digits below x = -6.)
+// and 8 weighted by the absolute error alone, 374 and 638 us where these take
+// 404 and 678 us on the same box, N = 500,000, K = 256, F = 1024, lose all digits
+// below x = -6.)
 // From z = 13 exp2 has no normal result and both are 0 (below 1e-36; slope 1
 // for x > 0).  The clamp keeps the polynomials finite and propagates NaN (IEEE
 // minimum): GELU(+inf) = inf, GELU(-inf) = 0.

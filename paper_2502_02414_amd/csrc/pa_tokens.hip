@@ -3,7 +3,7 @@
 // double, pa_tokens64.hip).  These products are tiny (M x C by C x C at most)
 // and bound by latency: a kernel is one round of loads, a short MFMA chain
 // (v_mfma_f32_16x16x4_f32) and its stores, and the work is spread over as many
-// CUs as it has 16 x 16 tiles.
+// CUs as it has 16 x 16 tiles (k_core_bwd: over one block per head).
 //   k_proj         out_p = In_p op(W_p) + b_p (op = W or W^T): a block per tile
 //   k_core         per head h (channels [hD, hD + D)) and 16 query rows, one
 //                  wave: P_h = softmax(Q_h K_h^T / sqrt(D)), O_h = P_h V_h

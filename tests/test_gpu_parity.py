@@ -180,8 +180,8 @@ def test_token_attention_backward(cases, shape):
     check_key_bias(ga["dbk"], ga["dbq"])
 
 
-# heads too large (D = C) or too narrow (D = 2) for the fused per-head
-# kernels: the general projection + core kernels
+# one head of all channels (D = C), and heads narrower than a step of the
+# score contraction (D = 2)
 GENERAL_HEADS = [(300, 128, 1, 64, "f32"), (300, 32, 16, 8, "f32")]
 
 
