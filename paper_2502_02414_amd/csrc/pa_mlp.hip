@@ -63,8 +63,8 @@ namespace {
 //   GELU   7.0e-7 for z < 1, 3.8e-5 up to 3, 2.4e-4 up to 5, 1.5e-3 up to 12.9
 //   GELU'  1.4e-7 absolute up to z = 3, 2.2e-5 up to 4, 5.1e-5 up to 6, 2.7e-4
 //          up to 13
-// and absolute at most 1.5e-7 and 1.1e-7 (x > 0: relative 5e-7 and 3e-7); half
-// a bf16 step is 2e-3 to 3.9e-3 of a value.  The rational erf of Abramowitz and Stegun
+// and absolute at most 1.6e-7 (of the value where that exceeds 1) and 1.8e-7 (x
+// > 0: relative 5e-7 and 3e-7); half a bf16 step is 2e-3 to 3.9e-3 of a value.  The rational erf of Abramowitz and Stegun
 // 7.1.26, evaluated the same way, has 7.0e-7, 5.2e-5, 1.6e-3, 3.7e-2 and, for
 // the slope, 3.0e-5, 1.0e-4, 2.3e-4, and takes a reciprocal more.  (Degrees 7
 // and 8 weighted by the absolute error alone, 374 and 638 us where these take
