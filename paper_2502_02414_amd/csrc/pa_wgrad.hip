@@ -558,11 +558,12 @@ hipError_t launch_wgrad(int64_t m, int64_t n, int64_t k, float alpha, const void
 
 // Groups: as many as keep a thread's loads few (256 Ki outputs, 62 partials: one
 // group 12.5 us, 4 and 8 10.7, 16 11.4; 16 Ki outputs, 250 partials: 28, 8.2, 5.3
-// and 3.9; 2 Mi outputs, 4 partials: 5.1 with one group, 8.5 with 4).
+// and 3.9, 125 partials 15, 5.1, 5.0 and 3.5; 2 Mi outputs, 4 partials: 5.1 with one
+// group, 8.5 with 4).
 hipError_t launch_add_parts(const float* parts, int P, int64_t outputs, float* D, hipStream_t st) {
   if (!parts || !D || P < 1 || outputs < 4 || outputs % 4 || outputs > (2 << 20))
     return hipErrorInvalidValue;
-  return P >= 128 ? launch_add<16>(parts, P, outputs / 4, D, st)
+  return P >= 96 ? launch_add<16>(parts, P, outputs / 4, D, st)
          : P >= 8 ? launch_add<8>(parts, P, outputs / 4, D, st)
                   : launch_add<1>(parts, P, outputs / 4, D, st);
 }

@@ -270,11 +270,11 @@ WGRADS = [  # m, n, k, dtype, workspace bytes
     # tiles of 256 columns (k m n >= 1.6e10) of 256, 128 and 64 rows
     (1024, 256, 61037, "bf16", 1 << 26), (384, 1024, 40691, "bf16", 1 << 26),
     (192, 1024, 81381, "bf16", 1 << 26),
-    # 2, 7 and 8, 127 and 128, 256 partials (added by one, eight and sixteen
+    # 2, 7 and 8, 95 and 96, 256 partials (added by one, eight and sixteen
     # groups); hipBLASLt's, for outputs that fill no block and of odd size
     (1024, 2048, 4128, "bf16", 1 << 26), (512, 256, 1025, "bf16", 1 << 24),
-    (512, 256, 1301, "bf16", 1 << 24), (64, 64, 4033, "f32", 1 << 24),
-    (64, 64, 4065, "f32", 1 << 24), (64, 64, 16384, "f32", 1 << 24),
+    (512, 256, 1301, "bf16", 1 << 24), (64, 64, 3033, "f32", 1 << 24),
+    (64, 64, 3065, "f32", 1 << 24), (64, 64, 16384, "f32", 1 << 24),
     (100, 70, 131100, "f32", 1 << 24), (33, 35, 131100, "f32", 1 << 24),
 ]
 
